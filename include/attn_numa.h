@@ -162,6 +162,32 @@ int attn_fwd_lse(const void *q, const void *k, const void *v, void *o, float *ls
                  int causal, float scale, int mapping);
 
 /*
+ * attn_fwd_ws -- attn_fwd (lse == NULL) or attn_fwd_lse with a workspace.
+ * Without a causal mask and with few query rows -- at most 32 per K/V head
+ * ((Hq/Hkv)*Sq: decoding steps), or few enough 32-row tiles in all that they
+ * run at once -- it cuts the keys over the waves of a workgroup and over several
+ * workgroups and merges their partial results, held in fp32 in the workspace,
+ * in a fixed order; every other call, and one whose workspace is too small,
+ * runs attn_fwd / attn_fwd_lse.  The cut changes the order of the fp32 sums, so
+ * such an output may differ from attn_fwd's by the rounding of those sums (and
+ * for d = 56 and 64 its lse is the fp32 sum of the fp32 exponentials, as for
+ * d = 128); it does not depend on the mapping and repeats bitwise.
+ *
+ * workspace : device pointer to workspace_bytes bytes, 16-byte aligned, owned
+ *     by the caller; its contents before and after the call mean nothing.  Must
+ *     not overlap any tensor.  May be NULL.  Calls that may overlap in time need
+ *     separate workspaces.
+ * Other arguments and behaviour as attn_fwd / attn_fwd_lse.
+ */
+int attn_fwd_ws(const void *q, const void *k, const void *v, void *o, float *lse, void *workspace,
+                int64_t workspace_bytes, int B, int Hq, int Hkv, int Sq, int Skv, int d, int causal,
+                float scale, int mapping);
+
+/* Workspace attn_fwd_ws can use for this shape (0: none), or a negative
+ * ATTN_ERR_* code for an invalid shape.  No HIP call is made. */
+int64_t attn_fwd_workspace_bytes(int B, int Hq, int Hkv, int Sq, int Skv, int d, int causal);
+
+/*
  * attn_bwd -- attention backward pass, Section 2.3 Eq. (2) ("eq:ba"), for the
  * forward of attn_fwd with the same (scale, causal, GQA grouping):
  *   P_ij  = exp(scale * s_ij - lse_i),  s_ij = <Q_i, K_j>

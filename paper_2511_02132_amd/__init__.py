@@ -94,6 +94,8 @@ SIGNATURES = {
     "attn_fwd_probe": ([_vp, _vp, _vp, _vp, _ci, _ci, _ci, _ci, _ci, _ci, _ci, _cf, _ci, _vp],
                        _ci),
     "attn_fwd_lse": ([_vp, _vp, _vp, _vp, _vp, _ci, _ci, _ci, _ci, _ci, _ci, _ci, _cf, _ci], _ci),
+    "attn_fwd_ws": ([_vp] * 6 + [ctypes.c_int64] + [_ci] * 7 + [_cf, _ci], _ci),
+    "attn_fwd_workspace_bytes": ([_ci] * 7, ctypes.c_int64),
     "attn_fwd_persistent": ([_vp] * 7 + [_ci, _ci, _ci, _ci, _ci, _ci, _ci, _cf, _ci], _ci),
     "attn_fwd_persistent_noalloc": ([_vp] * 6 + [_ci, _ci, _ci, _ci, _ci, _ci, _ci, _cf, _ci],
                                     _ci),
@@ -211,13 +213,32 @@ def _prepare(q, k, v, o, scale, stream):
     return o, (B, Hq, Hkv, Sq, Skv, d), float(scale)
 
 
+def _forward(what, q, k, v, o, lse, dims, causal, scale, mapping, stream):
+    """attn_fwd_ws with the workspace its split form asks for.  The workspace is
+    allocated on the stream the kernels run on, so that a later allocation that
+    gets its memory is ordered behind them."""
+    causal = 1 if causal else 0
+    ws, n = None, 0
+    if not causal:   # the split form exists without a mask only
+        n = lib().attn_fwd_workspace_bytes(*dims, causal)
+    if n > 0:
+        import torch
+        if stream is None:
+            ws = torch.empty(n, dtype=torch.uint8, device=q.device)
+        else:
+            with torch.cuda.stream(stream):
+                ws = torch.empty(n, dtype=torch.uint8, device=q.device)
+    _check(lib().attn_fwd_ws(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
+                             None if lse is None else lse.data_ptr(),
+                             None if ws is None else ws.data_ptr(), max(n, 0),
+                             *dims, causal, scale, int(mapping)), what)
+
+
 def attn_fwd(q, k, v, o=None, *, causal: bool = False, scale: float | None = None,
              mapping: int = SWIZZLED_HEAD_FIRST, stream=None):
     """O = softmax(scale * Q K^T [causal]) V on the GPU; returns o (enqueued, not synced)."""
-    o, (B, Hq, Hkv, Sq, Skv, d), scale = _prepare(q, k, v, o, scale, stream)
-    _check(lib().attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
-                          B, Hq, Hkv, Sq, Skv, d, int(bool(causal)), scale, int(mapping)),
-           "attn_fwd")
+    o, dims, scale = _prepare(q, k, v, o, scale, stream)
+    _forward("attn_fwd", q, k, v, o, None, dims, causal, scale, mapping, stream)
     return o
 
 
@@ -247,10 +268,8 @@ def attn_fwd_lse(q, k, v, o=None, lse=None, *, causal: bool = False, scale: floa
     if lse is None:
         lse = torch.empty((B, Hq, Sq), dtype=torch.float32, device=q.device)
     _check_stat(lse, (B, Hq, Sq), q.device, "lse")
-    _check(lib().attn_fwd_lse(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
-                              lse.data_ptr(), B, Hq, Hkv, Sq, Skv, d, int(bool(causal)), scale,
-                              int(mapping)),
-           "attn_fwd_lse")
+    _forward("attn_fwd_lse", q, k, v, o, lse, (B, Hq, Hkv, Sq, Skv, d), causal, scale, mapping,
+             stream)
     return o, lse
 
 

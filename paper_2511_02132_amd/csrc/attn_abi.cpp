@@ -12,8 +12,16 @@
 #include <cstring>
 
 #include "attn_calib.h"
+#include "attn_checks.h"
 #include "attn_internal.h"
 #include "attn_numa.h"
+
+using attn::check_shape;
+using attn::hip_fail;
+using attn::overlaps;
+using attn::supported_d;
+using attn::valid_mapping;
+using attn::validate;
 
 namespace {
 
@@ -23,8 +31,6 @@ thread_local char t_hip_error[256] = "";
 constexpr int kMaxDevices = 64;
 std::atomic<int> g_nx_cache[kMaxDevices];   // 0 = not yet queried
 std::atomic<int> g_cu_cache[kMaxDevices];   // compute units per device, 0 = not yet queried
-
-int hip_fail(hipError_t e);
 
 // Compute units of the current device (cached), or a negative ATTN_ERR_*.
 static_assert(ATTN_QUEUE_INTS == attn::kQueueInts && attn::kQueueDone < ATTN_QUEUE_INTS,
@@ -44,39 +50,6 @@ int num_cu() {
     return n;
 }
 
-int hip_fail(hipError_t e) {
-    std::snprintf(t_hip_error, sizeof t_hip_error, "%s (%d)", hipGetErrorString(e), (int)e);
-    return ATTN_ERR_HIP;
-}
-
-bool supported_d(int d) { return d == 56 || d == 64 || d == 128; }
-
-// Shape checks shared by every entry point.  Offsets inside one head are
-// 32-bit byte offsets, so a head (plus one tile of slack) must stay below 2^31.
-int check_shape(int B, int Hq, int Hkv, int Sq, int Skv, int d) {
-    if (B <= 0 || Hq <= 0 || Hkv <= 0 || Sq <= 0 || Skv <= 0 || d <= 0) return ATTN_ERR_SHAPE;
-    if (Hq % Hkv != 0) return ATTN_ERR_SHAPE;
-    if (!supported_d(d)) return ATTN_ERR_UNSUPPORTED;
-    const int64_t lim = INT32_MAX;
-    if (((int64_t)Sq + attn::kMaxBlockM) * d * 2 > lim) return ATTN_ERR_SHAPE;
-    if (((int64_t)Skv + 2 * attn::kBlockN) * d * 2 > lim) return ATTN_ERR_SHAPE;
-    const int bm = attn::block_m_for(d);
-    const int64_t nb = ((int64_t)Sq + bm - 1) / bm;
-    if ((int64_t)B * Hq * nb > lim) return ATTN_ERR_SHAPE;
-    return ATTN_OK;
-}
-
-// Base mapping in the low 4 bits, optional order flag above them.
-bool valid_mapping(int mapping) {
-    const int base = mapping & 0xf;
-    const int flags = mapping & ~0xf;
-    if (base < ATTN_MAP_NAIVE_BLOCK_FIRST || base > ATTN_MAP_SWIZZLED_BLOCK_FIRST) return false;
-    if ((flags & ~(ATTN_ORDER_HEAVY_FIRST | ATTN_ORDER_XCD_BLOCK_MAJOR | ATTN_ORDER_PAIRED)) != 0)
-        return false;
-    // the block-major order inside an XCD's piece is defined for mapping 2 only
-    return (flags & ATTN_ORDER_XCD_BLOCK_MAJOR) == 0 || base == ATTN_MAP_SWIZZLED_HEAD_FIRST;
-}
-
 int order_bits(int mapping) {
     return ((mapping & ATTN_ORDER_HEAVY_FIRST) ? attn::kOrderHeavyFirst : 0) |
            ((mapping & ATTN_ORDER_XCD_BLOCK_MAJOR) ? attn::kOrderXcdBlockMajor : 0) |
@@ -87,27 +60,6 @@ int order_bits(int mapping) {
 // pair slots of the paired order.
 int slots_per_head(int NB, int mapping) {
     return (mapping & ATTN_ORDER_PAIRED) ? attn::pair_slots(NB) : NB;
-}
-
-bool overlaps(const void *a, int64_t a_bytes, const void *b, int64_t b_bytes) {
-    const uintptr_t a0 = (uintptr_t)a, b0 = (uintptr_t)b;
-    return a0 < b0 + (uintptr_t)b_bytes && b0 < a0 + (uintptr_t)a_bytes;
-}
-
-int validate(const void *q, const void *k, const void *v, const void *o, int B, int Hq, int Hkv,
-             int Sq, int Skv, int d, float scale, int mapping) {
-    if (!q || !k || !v || !o) return ATTN_ERR_NULL;
-    int rc = check_shape(B, Hq, Hkv, Sq, Skv, d);
-    if (rc) return rc;
-    if (!valid_mapping(mapping)) return ATTN_ERR_MAPPING;
-    if (!std::isfinite(scale) || !(scale > 0.0f)) return ATTN_ERR_SCALE;
-    if (((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)o) & 15u) return ATTN_ERR_ALIGN;
-    const int64_t qo_bytes = (int64_t)B * Hq * Sq * d * 2;
-    const int64_t kv_bytes = (int64_t)B * Hkv * Skv * d * 2;
-    if (overlaps(o, qo_bytes, q, qo_bytes) || overlaps(o, qo_bytes, k, kv_bytes) ||
-        overlaps(o, qo_bytes, v, kv_bytes))
-        return ATTN_ERR_ALIAS;
-    return ATTN_OK;
 }
 
 int env_num_xcd() {
@@ -130,15 +82,8 @@ int run(const void *q, const void *k, const void *v, void *o, int B, int Hq, int
     // pairs exist for the dispatched head-dimension-128 kernel only
     if ((mapping & ATTN_ORDER_PAIRED) && (d != 128 || queue || use_static_queue))
         return ATTN_ERR_UNSUPPORTED;
-    if (lse) {
-        if (((uintptr_t)lse) & 3u) return ATTN_ERR_ALIGN;
-        const int64_t lse_bytes = (int64_t)B * Hq * Sq * 4;
-        const int64_t qo_bytes = (int64_t)B * Hq * Sq * d * 2;
-        const int64_t kv_bytes = (int64_t)B * Hkv * Skv * d * 2;
-        if (overlaps(lse, lse_bytes, q, qo_bytes) || overlaps(lse, lse_bytes, k, kv_bytes) ||
-            overlaps(lse, lse_bytes, v, kv_bytes) || overlaps(lse, lse_bytes, o, qo_bytes))
-            return ATTN_ERR_ALIAS;
-    }
+    rc = attn::validate_lse(lse, q, k, v, o, B, Hq, Hkv, Sq, Skv, d);
+    if (rc) return rc;
     const int nx = attn_num_xcd();
     if (nx < 0) return nx;
     attn::KernelArgs a{};   // every field zero (no probe, lse or queue) unless set below
@@ -181,6 +126,11 @@ int run(const void *q, const void *k, const void *v, void *o, int B, int Hq, int
 }
 
 }  // namespace
+
+int attn::hip_fail(hipError_t e) {
+    std::snprintf(t_hip_error, sizeof t_hip_error, "%s (%d)", hipGetErrorString(e), (int)e);
+    return ATTN_ERR_HIP;
+}
 
 extern "C" {
 

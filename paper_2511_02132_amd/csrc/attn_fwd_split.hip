@@ -1,0 +1,368 @@
+// attn_fwd_split.hip -- attention forward for few query rows against a long
+// K/V (decoding steps and the like), without a causal mask.
+//
+// Without a mask the query heads of a K/V head and their rows are one
+// contiguous run of R = (Hq/Hkv) * Sq rows that all see the same keys, so the
+// problem is B * Hkv independent products of R rows with Skv keys.  The other
+// kernels give each (b, hq) its own workgroup, which then walks all of K and V
+// alone: with one row per head their time is the length of that walk (128 tiles
+// of 64 keys at 8K, one after the other), every K/V row is copied once per query
+// head, and B * Hq workgroups are all there are.  Here each K/V row is copied
+// once per 32 packed rows, and the walk is cut two ways:
+//   * over the four waves of a workgroup, each with its own tiles of 32 keys,
+//     its own LDS stages and its own online-softmax state, merged through LDS at
+//     the end: no barrier inside the loop;
+//   * over `splits` workgroups per (b, K/V head, 32 rows), whose unnormalised
+//     results go to the caller's workspace in fp32 and are merged by a second,
+//     small kernel in a fixed order (so results do not depend on timing).
+// With every unit busy the kernel is bound by the K/V stream: a wave keeps one
+// tile (16 KiB at d = 128) in flight while it computes another, 64-128 KiB per
+// CU, which covers the memory latency.  B 32 Hq 64 Hkv 8 Sq 1 Skv 8192 d 128:
+// 179 us, 6.0 TB/s (a large device copy: 4.9 TB/s); B 4: 23.3 us and 4.0 us for
+// the merge.  Fewer keys than that are bound by a workgroup's start (about 4 us)
+// and its waves' tiles (about 1 us each).
+//
+// Per tile a wave computes S^T = K Q^T, the softmax and O^T += V^T P^T exactly
+// like attn_fwd_pp.hip (same layouts, same lazily raised reference maximum, fp32
+// row sum), with 32 keys instead of 64.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "attn_device.h"
+#include "attn_internal.h"
+#include "attn_numa.h"
+
+namespace attn {
+namespace {
+
+using namespace dev;
+
+constexpr int kSplitWaves = 4;
+constexpr int kSplitThreads = 64 * kSplitWaves;
+constexpr int kStagesPerWave = 2;
+
+// LDS of one wave: two stages of a K and a V tile (32 keys); after the loop its
+// 32 x D fp32 output and its row statistics take their place.
+constexpr int wave_lds_bytes(int D) { return kStagesPerWave * 2 * kSplitKeys * D * 2; }
+
+// Weight of a partial result with reference m in a sum taken against M >= m
+// (log2 domain); a part that saw no finite score (m = -inf) has weight 0.
+__device__ __forceinline__ float part_weight(float m, float M) {
+    return m == -__builtin_inff() ? 0.0f : exp2_hw(m - M);
+}
+
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// D: head dimension computed with; DG <= D: that of the tensors (as in
+// attn_fwd.hip: missing 16-byte chunks are read as zeros).
+template <int D, int DG>
+__global__ __launch_bounds__(kSplitThreads, D == 128 ? 1 : 2) void attn_fwd_split_kernel(
+    const SplitArgs p) {
+    constexpr int BN = kSplitKeys;
+    constexpr int ROW_BYTES = D * 2;
+    constexpr int ROW_BYTES_G = DG * 2;
+    constexpr int CHUNKS = D / 8;
+    constexpr int CHUNKS_G = DG / 8;
+    constexpr int KSTEPS = D / 16;
+    constexpr int DBLK = D / 32;
+    constexpr int TILE = BN * ROW_BYTES;
+    constexpr int STAGE = 2 * TILE;
+    constexpr int WAVE_LDS = wave_lds_bytes(D);
+    constexpr int COPIES = TILE / 1024;            // copy instructions per K or V tile
+    constexpr uint32_t kOutOfRange = 0x80000000u;
+    static_assert(32 * D * 4 <= WAVE_LDS, "a wave's output takes the place of its stages");
+
+    __shared__ __attribute__((aligned(1024))) char smem[kSplitWaves * WAVE_LDS];
+    __shared__ float stat[kSplitWaves][32][2];     // (reference, row sum) per wave and row
+    lds_char *const lds = (lds_char *)smem;
+    const uint32_t lds_base = (uint32_t)(uintptr_t)lds;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 31;
+    const int h = lane >> 5;
+
+    // The placement of the forward's mapping over (b, K/V head, split and row
+    // tile): with the swizzled mappings the row tiles and splits of a K/V head
+    // stay on one XCD.
+    const Tile t = map_wid(p.mapping, 0, blockIdx.x, p.B, p.Hkv, p.splits * p.MB, p.NX);
+    const int split = t.m / p.MB;
+    const int r0 = (t.m % p.MB) * 32;
+    const int64_t head = (int64_t)t.b * p.Hkv + t.hq;
+
+    auto mem_chunk = [&](const int row, const int ch) -> uint32_t {
+        return ch < CHUNKS_G ? (uint32_t)(row * ROW_BYTES_G + ch * 16) : kOutOfRange;
+    };
+
+    // Key tiles of this split: [tile0, tile1) of 32 keys; wave w takes tile0 + w,
+    // tile0 + w + 4, ...
+    const int tiles = (p.Skv + BN - 1) / BN;
+    const int tile0 = min(split * p.tiles_per_split, tiles);
+    const int tile1 = min(tile0 + p.tiles_per_split, tiles);
+    const int first = tile0 + w;
+    const int n_mine = first < tile1 ? (tile1 - first + kSplitWaves - 1) / kSplitWaves : 0;
+
+    uint32_t k_src[COPIES], v_src[COPIES];
+#pragma unroll
+    for (int i = 0; i < COPIES; ++i) {
+        const int slot = i * 64 + lane;
+        const int row = slot / CHUNKS;
+        const int phys = slot % CHUNKS;
+        k_src[i] = mem_chunk(row, phys ^ k_swizzle<D>(row));
+        const int seg = (phys >> 1) ^ v_swizzle<D>(row);
+        v_src[i] = mem_chunk(row, seg * 2 + (phys & 1));
+    }
+    const char *const k_head = (const char *)p.k + head * p.Skv * ROW_BYTES_G;
+    const char *const v_head = (const char *)p.v + head * p.Skv * ROW_BYTES_G;
+    const uint32_t kv_bytes = (uint32_t)p.Skv * ROW_BYTES_G;
+    const uint32_t wave_base = lds_base + w * WAVE_LDS;
+    // This wave's i-th tile into stage i % 2 of its own LDS.
+    auto copy = [&](const int i) __attribute__((always_inline)) {
+        const uint32_t off = (uint32_t)(first + i * kSplitWaves) * (BN * ROW_BYTES_G);
+        const uint32_t dst = wave_base + (i % kStagesPerWave) * STAGE;
+        const i32x4 dk = buffer_words(k_head + off, kv_bytes - off);
+        const i32x4 dv = buffer_words(v_head + off, kv_bytes - off);
+#pragma unroll
+        for (int j = 0; j < COPIES; ++j) lds_copy16(dk, k_src[j], dst + j * 1024);
+#pragma unroll
+        for (int j = 0; j < COPIES; ++j) lds_copy16(dv, v_src[j], dst + TILE + j * 1024);
+    };
+    if (n_mine > 0) copy(0);
+
+    // Packed rows r0 + c; rows past R read zeros and are not stored.
+    const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)((const char *)p.q + head * p.R * ROW_BYTES_G), 0, p.R * ROW_BYTES_G, kBufferFlags);
+    bf16x8 qreg[KSTEPS];
+#pragma unroll
+    for (int kk = 0; kk < KSTEPS; ++kk)
+        qreg[kk] = __builtin_bit_cast(bf16x8, load16(rq, mem_chunk(r0 + c, 2 * kk + h)));
+
+    uint32_t k_off[KSTEPS];
+#pragma unroll
+    for (int kk = 0; kk < KSTEPS; ++kk)
+        k_off[kk] = c * ROW_BYTES + (((2 * kk + h) ^ k_swizzle<D>(c)) * 16);
+    const int li = lane & 15;
+    const int gsel = (lane >> 4) & 1;
+    uint32_t v_off[DBLK];
+#pragma unroll
+    for (int db = 0; db < DBLK; ++db)
+        v_off[db] = (4 * h + (li >> 2)) * ROW_BYTES + 8 * (li & 3) +
+                    (((2 * db + gsel) ^ v_swizzle<D>(4 * h + (li >> 2))) * 32);
+
+    f32x16 oacc[DBLK];
+#pragma unroll
+    for (int db = 0; db < DBLK; ++db)
+        for (int r = 0; r < 16; ++r) oacc[db][r] = 0.0f;
+    float mb = -__builtin_inff();   // reference, times scale * log2(e)
+    float lsum = 0.0f;
+    const float sl2 = p.scale_log2;
+
+    for (int i = 0; i < n_mine; ++i) {
+        if (i + 1 < n_mine) {
+            copy(i + 1);
+            wait_vmcnt<2 * COPIES>();   // tile i has landed; tile i + 1 stays in flight
+        } else {
+            wait_vmcnt<0>();
+        }
+        lds_char *const kb = lds + w * WAVE_LDS + (i % kStagesPerWave) * STAGE;
+        lds_char *const vb = kb + TILE;
+        f32x16 s = {};
+#pragma unroll
+        for (int kk = 0; kk < KSTEPS; ++kk) {
+            const bf16x8 a = *(const lds_bf16x8 *)(kb + k_off[kk]);
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qreg[kk], s, 0, 0, 0);
+        }
+        const int key0 = (first + i * kSplitWaves) * BN;
+        if (key0 + BN > p.Skv) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (key0 + 8 * (r >> 2) + 4 * h + (r & 3) >= p.Skv) s[r] = -__builtin_inff();
+        }
+        f32x8 p8[2];
+        auto exps = [&](const float ref) __attribute__((always_inline)) {
+            float ts = 0.0f;
+#pragma unroll
+            for (int kc = 0; kc < 2; ++kc)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    p8[kc][e] = exp2_hw(__builtin_fmaf(s[8 * kc + e], sl2, -ref));
+                    ts += p8[kc][e];
+                }
+            return ts;
+        };
+        float tsum = exps(mb);
+        if (__any(!(tsum <= 16777216.0f))) {
+            float mx = s[0];
+#pragma unroll
+            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+            const float mb_new = fmaxf(mb, fmaxf(mx, xor32(mx)) * sl2);
+            // A row whose scores so far are all -inf keeps its reference unset:
+            // its exponentials are 0, and the next tile comes here again.
+            const float alpha = part_weight(mb, mb_new);
+            lsum *= alpha;
+#pragma unroll
+            for (int db = 0; db < DBLK; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
+            mb = mb_new;
+            tsum = exps(mb_new == -__builtin_inff() ? 0.0f : mb_new);
+        }
+        lsum += tsum;
+        bf16x8 pb[2];
+#pragma unroll
+        for (int kc = 0; kc < 2; ++kc) pb[kc] = __builtin_convertvector(p8[kc], bf16x8);
+#pragma unroll
+        for (int kc = 0; kc < 2; ++kc)
+#pragma unroll
+            for (int db = 0; db < DBLK; ++db) {
+                const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+                    (lds_bf16x4 *)(vb + v_off[db] + 16 * kc * ROW_BYTES));
+                const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+                    (lds_bf16x4 *)(vb + v_off[db] + (16 * kc + 8) * ROW_BYTES));
+                const bf16x8 a = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+                oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pb[kc], oacc[db], 0, 0, 0);
+            }
+        // the reads of this stage have returned before the next trip's copy
+        // into it is issued
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+
+    // Merge the four waves.  Each wave's copies have landed and its reads have
+    // returned, so its own stages take its output: row c, fp32 chunk q (four
+    // columns) at q ^ (c mod chunks).
+    constexpr int OROW = D * 4;
+    constexpr int OCH = D / 4;
+    lds_char *const ow = lds + w * WAVE_LDS;
+#pragma unroll
+    for (int db = 0; db < DBLK; ++db)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const f32x4 v4 = {oacc[db][4 * j + 0], oacc[db][4 * j + 1], oacc[db][4 * j + 2],
+                              oacc[db][4 * j + 3]};
+            const int q = 8 * db + 2 * j + h;
+            *(lds_f32x4 *)(ow + c * OROW + ((q ^ (c & (OCH - 1))) * 16)) = v4;
+        }
+    const float l_row = lsum + xor32(lsum);
+    if (lane < 32) {
+        stat[w][c][0] = mb;
+        stat[w][c][1] = l_row;
+    }
+    __syncthreads();
+
+    // Thread: row tid / 8, chunks tid % 8, tid % 8 + 8, ...
+    const int row = tid >> 3;
+    float M = -__builtin_inff();
+#pragma unroll
+    for (int i = 0; i < kSplitWaves; ++i) M = fmaxf(M, stat[i][row][0]);
+    float wt[kSplitWaves];
+    float L = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kSplitWaves; ++i) {
+        wt[i] = part_weight(stat[i][row][0], M);
+        L += wt[i] * stat[i][row][1];
+    }
+    const int64_t out_row = head * p.R + r0 + row;
+    if (r0 + row >= p.R) return;
+    const float inv = 1.0f / L;
+#pragma unroll
+    for (int j = 0; j < OCH / 8; ++j) {
+        const int q = (tid & 7) + 8 * j;
+        if (4 * q >= DG) continue;
+        f32x4 v4 = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int i = 0; i < kSplitWaves; ++i) {
+            const f32x4 x = *(const lds_f32x4 *)(lds + i * WAVE_LDS + row * OROW +
+                                                 ((q ^ (row & (OCH - 1))) * 16));
+            // a wave without a tile holds zeros
+            v4 += wt[i] * x;
+        }
+        if (p.part == nullptr) {
+            v4 *= inv;
+            const bf16x4 b4 = __builtin_convertvector(v4, bf16x4);
+            *(u32x2 *)((char *)p.o + out_row * ROW_BYTES_G + q * 8) = __builtin_bit_cast(u32x2, b4);
+        } else {
+            *(f32x4 *)(p.part + (out_row * p.splits + split) * DG + 4 * q) = v4;
+        }
+    }
+    if ((tid & 7) == 0) {
+        if (p.part == nullptr) {
+            if (p.lse != nullptr) p.lse[out_row] = (M + log2_hw(L)) * kLn2;
+        } else {
+            float *const st = p.part_stat + (out_row * p.splits + split) * 2;
+            st[0] = M;
+            st[1] = L;
+        }
+    }
+}
+
+// Merge of a row's splits: one wave per row, lanes over columns.
+template <int DG>
+__global__ __launch_bounds__(256) void attn_fwd_merge_kernel(const SplitArgs p) {
+    const int64_t rows = (int64_t)p.B * p.Hkv * p.R;
+    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (row >= rows) return;
+    const float *const st = p.part_stat + row * p.splits * 2;
+    // splits <= 64: lane i holds split i's statistics
+    const float m = lane < p.splits ? st[2 * lane] : -__builtin_inff();
+    const float l = lane < p.splits ? st[2 * lane + 1] : 0.0f;
+    float M = m;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) M = fmaxf(M, __shfl_xor(M, d, 64));
+    const float wt = part_weight(m, M);
+    float L = wt * l;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) L += __shfl_xor(L, d, 64);
+    constexpr int PER = DG == 128 ? 2 : 1;   // columns per lane
+    const int col = lane * PER;
+    float acc[PER] = {};
+    const float *const src = p.part + row * p.splits * DG + col;
+    const bool live = col < DG;
+    // eight splits' loads in flight at a time
+    for (int s0 = 0; s0 < p.splits; s0 += 8) {
+        float x[8][PER] = {};
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (live && s0 + u < p.splits)
+#pragma unroll
+                for (int e = 0; e < PER; ++e) x[u][e] = src[(s0 + u) * DG + e];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const float f = __shfl(wt, s0 + u, 64);   // 0 past the last split
+#pragma unroll
+            for (int e = 0; e < PER; ++e) acc[e] += f * x[u][e];
+        }
+    }
+    if (live) {
+        __bf16 *const o = (__bf16 *)p.o + row * DG + col;
+#pragma unroll
+        for (int e = 0; e < PER; ++e) o[e] = (__bf16)(acc[e] / L);
+    }
+    if (lane == 0 && p.lse != nullptr) p.lse[row] = (M + log2_hw(L)) * kLn2;
+}
+
+template <int D, int DG>
+hipError_t launch(const SplitArgs &a, hipStream_t stream) {
+    const int grid = a.B * a.Hkv * a.MB * a.splits;
+    hipLaunchKernelGGL((attn_fwd_split_kernel<D, DG>), dim3(grid), dim3(kSplitThreads), 0, stream, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || a.splits == 1) return e;
+    const int64_t rows = (int64_t)a.B * a.Hkv * a.R;
+    hipLaunchKernelGGL((attn_fwd_merge_kernel<DG>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0,
+                       stream, a);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_attn_fwd_split(const SplitArgs &a, int d, hipStream_t stream) {
+    if (d == 128) return launch<128, 128>(a, stream);
+    if (d == 64) return launch<64, 64>(a, stream);
+    return launch<64, 56>(a, stream);
+}
+
+}  // namespace attn

@@ -174,6 +174,26 @@ struct BwdArgs {
     float scale_log2;
 };
 
+// Split forward (attn_fwd_split.hip): B * Hkv products of R = (Hq/Hkv) * Sq
+// packed query rows with the keys of a K/V head, no mask.
+constexpr int kSplitKeys = 32;     // keys per tile of a wave
+constexpr int kMaxSplits = 64;     // the merge holds one split per lane
+struct SplitArgs {
+    const void *q;
+    const void *k;
+    const void *v;
+    void *o;
+    float *lse;         // NULL, or as KernelArgs
+    float *part;        // NULL (one split), or [rows][splits][d] fp32: unnormalised output
+    float *part_stat;   // [rows][splits][2]: reference (log2 domain) and row sum
+    int B, Hkv, R, Skv;
+    int MB;             // row tiles: ceil(R / 32)
+    int splits;         // workgroups along the keys, 1..kMaxSplits
+    int tiles_per_split;
+    int mapping, NX;
+    float scale_log2;
+};
+
 // Enqueue the forward kernel for head dimension d (64 or 128) and base mapping
 // 0..3 (one kernel instantiation per combination).
 hipError_t launch_attn_fwd(const KernelArgs &args, int d, bool causal, int mapping, int grid,
@@ -181,6 +201,8 @@ hipError_t launch_attn_fwd(const KernelArgs &args, int d, bool causal, int mappi
 // The head-dimension-128 kernel (attn_fwd_pp.hip).
 hipError_t launch_attn_fwd_d128(const KernelArgs &args, bool causal, int mapping, int grid,
                                 hipStream_t stream);
+// The split forward, and the merge of its splits when there are several.
+hipError_t launch_attn_fwd_split(const SplitArgs &args, int d, hipStream_t stream);
 // Device address of the library-owned tile-queue array (kQueueInts int32) on
 // the current device, looked up once per device (attn_fwd_pp.hip).
 hipError_t static_queue(int **queue);

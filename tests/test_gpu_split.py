@@ -1,0 +1,124 @@
+"""The split forward (few query rows, keys cut over waves and workgroups) against
+the fp64 oracle and against the kernels of the C entry attn_fwd.
+
+Bars as in test_gpu_attention.py (O: max 2e-2, mean 2e-3); the row log-sum-exp is
+an fp32 sum of fp32 exponentials for every head dimension: 1e-4.  Two correct
+outputs differ by their errors against the oracle: at most twice the O bar.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+import attn_inputs as ai
+import oracle
+import paper_2511_02132_amd as pa
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+MAX_ABS, MEAN_ABS, LSE_ABS = 2e-2, 2e-3, 1e-4
+
+SHAPES = [
+    # B, Hq, Hkv, Sq, Skv: edges of the 32-row and 32-key tiles, of the four waves'
+    # shares (128 keys) and of the splits; GQA rows packed over heads and rows
+    (1, 1, 1, 1, 1), (2, 2, 2, 1, 31), (1, 3, 3, 32, 32), (1, 4, 2, 16, 33), (1, 4, 1, 9, 97),
+    (2, 8, 2, 1, 128), (1, 8, 2, 8, 129), (1, 2, 2, 33, 300), (1, 16, 2, 5, 257),
+    (1, 8, 1, 1, 2049), (3, 6, 3, 2, 1500), (1, 4, 4, 100, 700),
+    (1, 2, 1, 1, 9000),     # the largest number of splits
+    (40, 8, 8, 3, 70),      # more workgroups than run at once
+]
+
+
+def _plan_splits(B, Hq, Hkv, Sq, Skv, d):
+    n = pa.lib().attn_fwd_workspace_bytes(B, Hq, Hkv, Sq, Skv, d, 0)
+    return n // (B * Hq * Sq * (d + 2) * 4)
+
+
+@pytest.mark.parametrize("d", [128, 64, 56])
+@pytest.mark.parametrize("B,Hq,Hkv,Sq,Skv", SHAPES)
+def test_split_forward(B, Hq, Hkv, Sq, Skv, d):
+    print("split", B, Hq, Hkv, Sq, Skv, d, "splits", _plan_splits(B, Hq, Hkv, Sq, Skv, d),
+          flush=True)
+    qc, kc, vc = ai.make_qkv(B, Hq, Hkv, Sq, Skv, d, seed_base=5000 + Sq + 7 * Skv)
+    scale = ai.default_scale(d)
+    q, k, v = qc.to(DEV), kc.to(DEV), vc.to(DEV)
+    bits = [ai.bf16_bits(t) for t in (qc, kc, vc)]
+    ref = oracle.attn_fwd_f64(*bits, False, scale)
+    ref_lse, _ = oracle.attn_row_stats_f64(*bits, None, oracle.all_rows(B, Hq, Sq), False, scale)
+    first = None
+    for mapping in (2, 0, 1, 3, 0x12, 0x32):
+        o = torch.full_like(q, float("nan"))
+        lse = torch.full((B, Hq, Sq), float("nan"), dtype=torch.float32, device=DEV)
+        pa.attn_fwd_lse(q, k, v, o, lse, scale=scale, mapping=mapping)
+        plain = pa.attn_fwd(q, k, v, scale=scale, mapping=mapping)
+        torch.cuda.synchronize()
+        if first is None:
+            first = o
+            err = np.abs(o.float().cpu().numpy().astype(np.float64) - ref)
+            assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (err.max(), err.mean())
+            got = lse.cpu().numpy().astype(np.float64).ravel()
+            assert np.abs(got - ref_lse).max() <= LSE_ABS
+        assert torch.equal(o, first) and torch.equal(plain, first), mapping
+    # the kernels of the C entry without a workspace
+    old = torch.full_like(q, float("nan"))
+    assert pa.lib().attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), old.data_ptr(), B, Hq, Hkv,
+                             Sq, Skv, d, 0, scale, 2) == 0
+    torch.cuda.synchronize()
+    assert (old.float() - first.float()).abs().max() <= 2 * MAX_ABS
+
+
+def test_split_runs_and_splits_where_it_should():
+    assert _plan_splits(1, 2, 1, 1, 9000, 128) > 8
+    assert _plan_splits(4, 64, 8, 1, 8192, 128) > 1
+    assert _plan_splits(32, 64, 8, 1, 8192, 128) == 0     # every unit busy without a cut
+
+
+def test_split_large_scores_and_infinite_keys():
+    """A wave's keys may all score far below another's, or -inf for a row: such a part
+    counts nothing and leaves the rest exact."""
+    B, H, Sq, Skv, d = 1, 2, 3, 1000, 128
+    qc, kc, vc = ai.make_qkv(B, H, H, Sq, Skv, d, seed_base=6200)
+    qc = qc.abs()
+    scale = ai.default_scale(d)
+    kc[:, :, 32:64] *= 64           # one wave's tile dominates
+    ref = oracle.attn_fwd_f64(*[ai.bf16_bits(t) for t in (qc, kc, vc)], False, scale)
+    o = pa.attn_fwd(qc.to(DEV), kc.to(DEV), vc.to(DEV), scale=scale)
+    err = np.abs(o.float().cpu().numpy().astype(np.float64) - ref)
+    assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS
+    # keys at -inf score (q >= 0): as if they were not there
+    keep = torch.ones(Skv, dtype=torch.bool)
+    keep[32:64] = False             # all of one wave's first tile
+    keep[500:] = False              # whole splits
+    kc2 = kc.clone()
+    kc2[:, :, ~keep] = float("-inf")
+    qc2 = qc + 0.125                # strictly positive: no 0 * inf
+    ref = oracle.attn_fwd_f64(ai.bf16_bits(qc2), ai.bf16_bits(kc2[:, :, keep]),
+                              ai.bf16_bits(vc[:, :, keep]), False, scale)
+    o = pa.attn_fwd(qc2.to(DEV), kc2.to(DEV), vc.to(DEV), scale=scale)
+    err = np.abs(o.float().cpu().numpy().astype(np.float64) - ref)
+    assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS
+
+
+def test_split_on_a_side_stream_and_in_a_graph():
+    q, k, v = [t.to(DEV) for t in ai.make_qkv(1, 8, 2, 1, 3000, 128, seed_base=6300)]
+    want = pa.attn_fwd(q, k, v)
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    outs = [torch.full_like(q, float("nan")) for _ in range(4)]
+    s.wait_stream(torch.cuda.current_stream())
+    for o in outs:
+        pa.attn_fwd(q, k, v, o, stream=s)
+    s.synchronize()
+    assert all(torch.equal(o, want) for o in outs)
+    g = torch.cuda.CUDAGraph()
+    o = torch.full_like(q, float("nan"))
+    with torch.cuda.graph(g):
+        pa.attn_fwd(q, k, v, o)
+    for seed in (1, 2, 3):          # replays on new inputs, with eager work between
+        q.copy_(ai.randn_bf16(tuple(q.shape), seed).to(DEV))
+        o.fill_(float("nan"))
+        g.replay()
+        want = pa.attn_fwd(q, k, v)
+        torch.cuda.synchronize()
+        assert torch.equal(o, want)

@@ -1,0 +1,54 @@
+"""Host side of the split forward (attn_fwd_ws, attn_fwd_workspace_bytes): status
+codes before any HIP call, and the bounds of the plan (no GPU)."""
+
+import itertools
+
+import pytest
+
+import paper_2511_02132_amd as pa
+
+Q, K, V, O, L, W = (0x10000000 * i for i in range(1, 7))
+
+
+def call(q=Q, k=K, v=V, o=O, lse=None, ws=W, n=1 << 24, B=1, Hq=4, Hkv=2, Sq=1, Skv=4096, d=128,
+         causal=0, scale=0.088, mapping=2):
+    return pa.lib().attn_fwd_ws(q, k, v, o, lse, ws, n, B, Hq, Hkv, Sq, Skv, d, causal, scale,
+                                mapping)
+
+
+@pytest.mark.parametrize("kwargs,code", [
+    (dict(q=None), -1), (dict(o=None), -1), (dict(B=0), -2), (dict(Hq=3), -2), (dict(d=96), -3),
+    (dict(mapping=4), -4), (dict(mapping=0x20), -4), (dict(scale=0.0), -5), (dict(q=Q + 8), -6),
+    (dict(lse=L + 2), -6), (dict(ws=W + 8), -6), (dict(o=K), -8), (dict(lse=O), -8),
+    (dict(ws=Q), -8), (dict(ws=K), -8), (dict(ws=O), -8), (dict(lse=L, ws=L), -8),
+    (dict(d=64, mapping=0x42), -3), (dict(d=64, mapping=0x42, ws=None), -3),
+])
+def test_validation_codes(kwargs, code):
+    assert call(**kwargs) == code
+
+
+def test_workspace_plan_bounds():
+    """The workspace holds whole splits (1..64 of them, none empty: each has a tile of
+    32 keys), is small, and is asked for without a mask only."""
+    ws = pa.lib().attn_fwd_workspace_bytes
+    assert ws(0, 4, 2, 1, 64, 128, 0) == -2 and ws(1, 3, 2, 1, 64, 128, 0) == -2
+    assert ws(1, 4, 2, 1, 64, 96, 0) == -3
+    seen = set()
+    for B, (Hq, Hkv), Sq, Skv, d in itertools.product(
+            (1, 2, 7, 32, 300), ((1, 1), (8, 1), (12, 4), (64, 8), (128, 128)),
+            (1, 2, 5, 31, 32, 33, 100, 700, 3000), (1, 31, 32, 33, 127, 128, 129, 1000, 8192, 100000),
+            (56, 64, 128)):
+        n = ws(B, Hq, Hkv, Sq, Skv, d, 0)
+        assert ws(B, Hq, Hkv, Sq, Skv, d, 1) == 0
+        assert n >= 0
+        if n == 0:
+            continue
+        per_split = B * Hq * Sq * (d + 2) * 4
+        splits = n // per_split
+        assert n == splits * per_split and 2 <= splits <= 64
+        tiles = (Skv + 31) // 32
+        per = -(-tiles // splits)
+        assert per >= 4 and (splits - 1) * per < tiles
+        assert n <= 64 << 20
+        seen.add(splits)
+    assert len(seen) > 5
