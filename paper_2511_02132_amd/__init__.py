@@ -175,7 +175,8 @@ def map_tiles(mapping: int, B: int, Hq: int, Sq: int, d: int, NX: int) -> np.nda
     return out
 
 
-def _shapes(q, k, v, o):
+def _explain(q, k, v, o):
+    """Raise for the first of the tensors' properties that _shapes refuses."""
     import torch
     for name, t in (("q", q), ("k", k), ("v", v), ("o", o)):
         if not isinstance(t, torch.Tensor):
@@ -188,29 +189,48 @@ def _shapes(q, k, v, o):
             raise ValueError("%s must be contiguous (BHSD)" % name)
         if t.dim() != 4:
             raise ValueError("%s must be 4-D [B, H, S, d]" % name)
-    B, Hq, Sq, d = q.shape
-    Bk, Hkv, Skv, dk = k.shape
-    if tuple(v.shape) != tuple(k.shape) or Bk != B or dk != d:
+    if v.shape != k.shape or k.shape[0] != q.shape[0] or k.shape[3] != q.shape[3]:
         raise ValueError("k and v must be [B, Hkv, Skv, d] matching q")
-    if tuple(o.shape) != tuple(q.shape):
+    if o.shape != q.shape:
         raise ValueError("o must have q's shape")
-    if not (q.device == k.device == v.device == o.device):
-        raise ValueError("all tensors must be on one device")
-    return B, Hq, Hkv, Sq, Skv, d
+    raise ValueError("all tensors must be on one device")
+
+
+def _shapes(q, k, v, o):
+    # A small call's time is this function and the launch, so the checks are one
+    # expression; _explain names what failed.
+    import torch
+    T, bf16 = torch.Tensor, torch.bfloat16
+    if not (isinstance(q, T) and isinstance(k, T) and isinstance(v, T) and isinstance(o, T)
+            and q.dtype == bf16 and k.dtype == bf16 and v.dtype == bf16 and o.dtype == bf16
+            and q.is_cuda and k.is_cuda and v.is_cuda and o.is_cuda
+            and q.is_contiguous() and k.is_contiguous() and v.is_contiguous()
+            and o.is_contiguous()):
+        _explain(q, k, v, o)
+    qs, ks = q.shape, k.shape
+    if len(qs) != 4 or len(ks) != 4 or v.shape != ks or o.shape != qs or ks[0] != qs[0] \
+            or ks[3] != qs[3]:
+        _explain(q, k, v, o)
+    i = q.get_device()
+    if k.get_device() != i or v.get_device() != i or o.get_device() != i:
+        _explain(q, k, v, o)
+    return qs[0], qs[1], ks[1], qs[2], ks[2], qs[3]
 
 
 def _prepare(q, k, v, o, scale, stream):
     import torch
     if o is None:
         o = torch.empty_like(q)
-    B, Hq, Hkv, Sq, Skv, d = _shapes(q, k, v, o)
+    dims = _shapes(q, k, v, o)
     if scale is None:
-        scale = 1.0 / math.sqrt(d)
-    if stream is None:
-        stream = torch.cuda.current_stream(q.device)
-    torch.cuda.set_device(q.device)
-    lib().attn_set_stream(ctypes.c_void_p(stream.cuda_stream))
-    return o, (B, Hq, Hkv, Sq, Skv, d), float(scale)
+        scale = 1.0 / math.sqrt(dims[5])
+    index = q.get_device()
+    # the stream's handle without a Stream object, when the caller names no stream
+    handle = torch._C._cuda_getCurrentRawStream(index) if stream is None else stream.cuda_stream
+    if torch._C._cuda_getDevice() != index:
+        torch.cuda.set_device(index)
+    lib().attn_set_stream(handle)
+    return o, dims, float(scale)
 
 
 def _forward(what, q, k, v, o, lse, dims, causal, scale, mapping, stream):

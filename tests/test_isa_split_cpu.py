@@ -1,0 +1,43 @@
+"""The machine-code checks of test_isa_cpu.py for the split forward (CPU only)."""
+
+import re
+import subprocess
+
+import pytest
+
+isa = pytest.importorskip("test_isa_cpu")   # not on a machine that only runs GPU tests
+B = isa.B
+
+pytestmark = pytest.mark.skipif(not isa._have_hipcc(), reason="hipcc not installed")
+
+
+def test_split_kernels_machine_code(tmp_path):
+    name = "attn_fwd_split.hip"
+    flags = [f for f in B.compile_flags(name) if f not in ("-fPIC", "-Wall")]
+    dst = tmp_path / "split.lst"
+    cmd = [B.hipcc(), *flags, "--cuda-device-only", "-S", B.CSRC + "/" + name, "-o", str(dst)]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+    text = dst.read_text()
+    copies = 0
+    for kname, body in isa._kernels(text):
+        for j, ins in enumerate(body):
+            op = ins.split()[0]
+            assert not isa.IMPLICIT_M0.match(op) and not isa.SCALAR_WRITE.match(op), (kname, ins)
+            assert not isa.PACKED_F32.match(op), (kname, ins)
+            if "m0" in ins.replace(",", " ").split():
+                assert op == "s_mov_b32" and body[j + 1] == "s_nop 4", (kname, ins)
+                assert re.search(r"^buffer_load_dwordx4.*\blds\b", body[j + 2]), body[j:j + 3]
+                copies += 1
+        if "merge" not in kname:
+            assert sum(i.startswith("v_mfma_f32_32x32x16_bf16") for i in body) >= 8, kname
+    assert copies > 0
+    mds = isa._metadata(text)
+    assert len(mds) == 6   # two kernels for each of d = 128, 64 and 56
+    for md in mds:
+        assert md["private_segment_fixed_size"] == "0" and md.get("vgpr_spill_count", "0") == "0"
+        assert int(md.get("agpr_count", "0")) == 0
+        lds = int(md["group_segment_fixed_size"])
+        # d = 128: one workgroup per CU; d = 64 and 56: two
+        per_cu = 1 if "ILi128ELi128E" in md["name"] else 2
+        assert per_cu * lds <= 160 * 1024 and int(md["vgpr_count"]) * per_cu <= 512, md["name"]
