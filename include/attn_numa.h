@@ -225,6 +225,26 @@ int attn_bwd(const void *q, const void *k, const void *v, const void *o, const v
              int causal, float scale, int mapping);
 
 /*
+ * attn_bwd_ws -- attn_bwd with a workspace.  When the key blocks are too few or
+ * too unequal to fill the chip, it cuts the query rows of a key block over
+ * several dK/dV workgroups, holds their parts in the workspace in fp32 and adds
+ * them in a fixed order.  Every other call, and one whose workspace is too
+ * small, runs attn_bwd.  The cut changes the order of dK's and dV's fp32 sums;
+ * the gradients do not depend on the mapping and repeat bitwise.
+ *
+ * workspace : as attn_fwd_ws; at least attn_bwd_workspace_bytes() bytes to be
+ *     used.  Other arguments and behaviour as attn_bwd.
+ */
+int attn_bwd_ws(const void *q, const void *k, const void *v, const void *o, const void *dout,
+                const float *lse, float *delta, void *dq, void *dk, void *dv, void *workspace,
+                int64_t workspace_bytes, int B, int Hq, int Hkv, int Sq, int Skv, int d, int causal,
+                float scale, int mapping);
+
+/* Workspace attn_bwd_ws can use for this shape (0: none), or a negative
+ * ATTN_ERR_* code for a shape attn_bwd refuses.  No HIP call is made. */
+int64_t attn_bwd_workspace_bytes(int B, int Hq, int Hkv, int Sq, int Skv, int d, int causal);
+
+/*
  * attn_fwd_persistent -- attn_fwd (optionally also writing lse, as
  * attn_fwd_lse) in a persistent, dispatch-independent form (head dimension 128
  * only): one workgroup per compute unit (or per tile, if there are fewer tiles)

@@ -100,6 +100,8 @@ SIGNATURES = {
     "attn_fwd_persistent_noalloc": ([_vp] * 6 + [_ci, _ci, _ci, _ci, _ci, _ci, _ci, _cf, _ci],
                                     _ci),
     "attn_bwd": ([_vp] * 10 + [_ci, _ci, _ci, _ci, _ci, _ci, _ci, _cf, _ci], _ci),
+    "attn_bwd_ws": ([_vp] * 11 + [ctypes.c_int64] + [_ci] * 7 + [_cf, _ci], _ci),
+    "attn_bwd_workspace_bytes": ([_ci] * 7, ctypes.c_int64),
     "attn_calib_mfma": ([_ci, _ci, _vp, _vp], _ci),
     "attn_grid_size": ([_ci, _ci, _ci, _ci], ctypes.c_int64),
     "attn_map_tiles": ([_ci, _ci, _ci, _ci, _ci, _ci, _i32p], _ci),
@@ -233,21 +235,28 @@ def _prepare(q, k, v, o, scale, stream):
     return o, dims, float(scale)
 
 
+def _workspace(n, device, stream):
+    """n bytes for kernels on `stream` (None: the current one), or None when there is
+    no memory left (the calls then do without).  Allocated on that stream, so that
+    a later allocation that gets the memory is ordered behind them."""
+    import torch
+    try:
+        if stream is None:
+            return torch.empty(n, dtype=torch.uint8, device=device)
+        with torch.cuda.stream(stream):
+            return torch.empty(n, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return None
+
+
 def _forward(what, q, k, v, o, lse, dims, causal, scale, mapping, stream):
-    """attn_fwd_ws with the workspace its split form asks for.  The workspace is
-    allocated on the stream the kernels run on, so that a later allocation that
-    gets its memory is ordered behind them."""
+    """attn_fwd_ws with the workspace its split form asks for."""
     causal = 1 if causal else 0
     ws, n = None, 0
     if not causal:   # the split form exists without a mask only
         n = lib().attn_fwd_workspace_bytes(*dims, causal)
     if n > 0:
-        import torch
-        if stream is None:
-            ws = torch.empty(n, dtype=torch.uint8, device=q.device)
-        else:
-            with torch.cuda.stream(stream):
-                ws = torch.empty(n, dtype=torch.uint8, device=q.device)
+        ws = _workspace(n, q.device, stream)
     _check(lib().attn_fwd_ws(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
                              None if lse is None else lse.data_ptr(),
                              None if ws is None else ws.data_ptr(), max(n, 0),
@@ -384,10 +393,13 @@ def attn_bwd(q, k, v, o, dout, lse, dq=None, dk=None, dv=None, delta=None, *,
     _shapes(dq, dk, dv, dq)
     _check_stat(lse, (B, Hq, Sq), q.device, "lse")
     _check_stat(delta, (B, Hq, Sq), q.device, "delta")
-    _check(lib().attn_bwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
-                          dout.data_ptr(), lse.data_ptr(), delta.data_ptr(), dq.data_ptr(),
-                          dk.data_ptr(), dv.data_ptr(), B, Hq, Hkv, Sq, Skv, d,
-                          int(bool(causal)), scale, int(mapping)),
+    causal = 1 if causal else 0
+    n = lib().attn_bwd_workspace_bytes(B, Hq, Hkv, Sq, Skv, d, causal)
+    ws = _workspace(n, q.device, stream) if n > 0 else None
+    _check(lib().attn_bwd_ws(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(),
+                             dout.data_ptr(), lse.data_ptr(), delta.data_ptr(), dq.data_ptr(),
+                             dk.data_ptr(), dv.data_ptr(), None if ws is None else ws.data_ptr(),
+                             max(n, 0), B, Hq, Hkv, Sq, Skv, d, causal, scale, int(mapping)),
            "attn_bwd")
     return dq, dk, dv
 

@@ -1,8 +1,9 @@
-// attn_abi_ws.cpp -- the forward entry point that may use a caller-owned
-// workspace (attn_fwd_ws) and the rule that decides when it runs the split
-// kernel (attn_fwd_split.hip) instead of the ones attn_fwd runs.
+// attn_abi_ws.cpp -- the entry points that may use a caller-owned workspace
+// (attn_fwd_ws, attn_bwd_ws) and the rules that decide when they cut the work of
+// a row tile or a key block over several workgroups.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "attn_checks.h"
@@ -18,6 +19,8 @@ struct SplitPlan {
 };
 
 constexpr int kComputeUnits = 256;
+constexpr int kMaxBwdParts = 16;   // parts per key block of the dK/dV kernel
+constexpr int64_t kMaxBwdBytes = (int64_t)512 << 20;
 // Longer runs of packed rows stay with the kernels of attn_fwd, whose output
 // the persistent form repeats bitwise.
 constexpr int kSplitMaxRows = 2048;
@@ -80,6 +83,72 @@ SplitPlan plan_split(int B, int Hq, int Hkv, int Sq, int Skv, int d, int causal)
     return s;
 }
 
+// Steps per part of the dK/dV kernel, 0 for one part per key block.
+//
+// One workgroup per key block leaves the chip idle when B * Hkv * (Skv / 128) is
+// small (grouped-query heads, short sequences), and under a mask the first key
+// blocks take longest.  The estimate below (us; a step takes 1.3 alone on a CU
+// and 2.0 beside a second workgroup) is evaluated for 1 to 16 parts of the
+// longest key block.  Whole backward pass, causal unless noted, us, one part ->
+// the chosen count (best count measured):
+//   B 1 H 32/8 S 4096       996 -> 582 (552)   B 1 H 8/1  S 2405    903 -> 144
+//   B 1 H 64/8 S 2000       832 -> 314 (290)   B 1 H 12/4 S 600     109 -> 46
+//   B 1 H 32/8 S 1024       222 -> 83          B 2 H 16/16 S 1111   107 -> 90
+//   B 1 H 32/8 S 8192      2271 -> 1875        B 1 H 32/32 S 4096   595 -> 593
+//   B 1 H 32/8 S 4096 no mask 963 -> 837       B 1 H 32/32 S 2048 no mask 231, one
+int plan_bwd_steps(int B, int Hq, int Hkv, int Sq, int Skv, int causal) {
+    const int NKV = (Skv + attn::kBwdKeys - 1) / attn::kBwdKeys;
+    const int64_t heads = (int64_t)B * Hkv;
+    const int longest = attn::bwd_steps(causal != 0, 0, Hq / Hkv, Sq);
+    if (heads * NKV > 4096 || (int64_t)Skv * attn::kBwdKeys * 4 > INT32_MAX / 2) return 0;
+    const int slots = 2 * kComputeUnits;
+    double best = 0.0;
+    int best_parts = 1;
+    for (int parts = 1; parts <= kMaxBwdParts; ++parts) {
+        const int len = (longest + parts - 1) / parts;
+        if (parts > 1 && (len < 4 || 1024 * heads * parts * Skv > kMaxBwdBytes)) break;
+        int64_t wgs = 0, steps = 0, written = 0;
+        for (int n = 0; n < NKV; ++n) {
+            const int st = attn::bwd_steps(causal != 0, n, Hq / Hkv, Sq);
+            const int pn = st > len ? (st + len - 1) / len : 1;
+            wgs += pn;
+            steps += st;
+            if (pn > 1) written += pn;
+        }
+        wgs *= heads;
+        steps *= heads;
+        written *= heads;
+        const double fill = wgs < slots ? (double)wgs / slots : 1.0;
+        const double step_us = 1.3 + 0.7 * fill;
+        // One round takes the longest workgroup.  Several, in order: under a mask,
+        // whose blocks differ, an even share and a part of the longest as the
+        // tail, or whole rounds of the mean; without one, whole rounds.
+        const int64_t rounds = (wgs + slots - 1) / slots;
+        double span = len;
+        if (rounds > 1 && causal) {
+            span = std::max(span, (double)steps / slots + 0.35 * len);
+            span = std::max(span, (double)rounds * steps / wgs);
+        } else if (rounds > 1) {
+            span = (double)rounds * len;
+        }
+        // each part: 128 KiB written and read again
+        const double t = span * step_us + (parts > 1 ? 2.0 + written * 0.05 : 0.0);
+        // a cut has to be worth its workspace
+        if (parts == 1 || t < (best_parts == 1 ? 0.95 * best : best)) {
+            best = t;
+            best_parts = parts;
+        }
+    }
+    return best_parts == 1 ? 0 : (longest + best_parts - 1) / best_parts;
+}
+
+int64_t bwd_parts_bytes(int B, int Hq, int Hkv, int Sq, int Skv, int causal, int steps) {
+    if (steps == 0) return 0;
+    const int longest = attn::bwd_steps(causal != 0, 0, Hq / Hkv, Sq);
+    const int parts = (longest + steps - 1) / steps;
+    return 2 * (int64_t)B * Hkv * parts * Skv * 128 * 4;
+}
+
 }  // namespace
 
 extern "C" {
@@ -137,6 +206,41 @@ int attn_fwd_ws(const void *q, const void *k, const void *v, void *o, float *lse
     a.NX = nx;
     a.scale_log2 = (float)((double)scale * 1.4426950408889634073599246810019);  // log2(e)
     const hipError_t e = attn::launch_attn_fwd_split(a, d, (hipStream_t)attn_get_stream());
+    return e == hipSuccess ? ATTN_OK : attn::hip_fail(e);
+}
+
+int64_t attn_bwd_workspace_bytes(int B, int Hq, int Hkv, int Sq, int Skv, int d, int causal) {
+    const int rc = attn::check_shape(B, Hq, Hkv, Sq, Skv, d);
+    if (rc) return rc;
+    if (d != 128) return ATTN_ERR_UNSUPPORTED;
+    return bwd_parts_bytes(B, Hq, Hkv, Sq, Skv, causal, plan_bwd_steps(B, Hq, Hkv, Sq, Skv, causal));
+}
+
+int attn_bwd_ws(const void *q, const void *k, const void *v, const void *o, const void *dout,
+                const float *lse, float *delta, void *dq, void *dk, void *dv, void *workspace,
+                int64_t workspace_bytes, int B, int Hq, int Hkv, int Sq, int Skv, int d, int causal,
+                float scale, int mapping) {
+    attn::BwdArgs a{};
+    const int rc = attn::prepare_bwd(a, q, k, v, o, dout, lse, delta, dq, dk, dv, B, Hq, Hkv, Sq,
+                                     Skv, d, scale, mapping);
+    if (rc) return rc;
+    const int steps = plan_bwd_steps(B, Hq, Hkv, Sq, Skv, causal);
+    const int64_t need = bwd_parts_bytes(B, Hq, Hkv, Sq, Skv, causal, steps);
+    if (need > 0 && workspace != nullptr && workspace_bytes >= need) {
+        if ((uintptr_t)workspace & 15u) return ATTN_ERR_ALIGN;
+        const int64_t qo = (int64_t)B * Hq * Sq * d * 2;
+        const int64_t kv = (int64_t)B * Hkv * Skv * d * 2;
+        const int64_t st = (int64_t)B * Hq * Sq * 4;
+        const void *other[10] = {q, k, v, o, dout, lse, delta, dq, dk, dv};
+        const int64_t bytes[10] = {qo, kv, kv, qo, qo, st, st, qo, kv, kv};
+        for (int i = 0; i < 10; ++i)
+            if (attn::overlaps(workspace, need, other[i], bytes[i])) return ATTN_ERR_ALIAS;
+        a.part_steps = steps;
+        a.parts = (attn::bwd_steps(causal != 0, 0, Hq / Hkv, Sq) + steps - 1) / steps;
+        a.part = (float *)workspace;
+    }
+    const hipError_t e =
+        attn::launch_attn_bwd(a, causal != 0, mapping & 0xf, (hipStream_t)attn_get_stream());
     return e == hipSuccess ? ATTN_OK : attn::hip_fail(e);
 }
 

@@ -15,13 +15,17 @@
 //      the FlashAttention-2 split of the backward over key blocks (Section
 //      2.3.1); it streams every query head of the group and every query tile
 //      of 32 rows through LDS, keeping the block's K and V rows in registers
-//      and dK, dV in fp32 accumulators, so a GQA group's sum needs no atomics;
+//      and dK, dV in fp32 accumulators, so a GQA group's sum needs no atomics.
+//      Where key blocks are too few or too unequal to fill the chip, a key
+//      block's (query head, query tile) steps are cut into parts of equal length,
+//      one workgroup each, whose fp32 results the dQ launch adds up in order
+//      (the caller gives a workspace; attn_abi_ws.cpp holds the rule);
 //   3. dQ: one workgroup per (b, query head, block of 128 rows), streaming
 //      K and V tiles of 64 keys like the forward, dQ accumulated in registers
 //      (attn_bwd_dq.hip, built with its own register-class option).
 // Splitting dQ from dK/dV recomputes S and dP once more, but every output is
-// written by exactly one workgroup in a fixed order: the gradients are
-// deterministic and bitwise independent of the workgroup mapping.
+// summed in an order fixed by the shape and written by exactly one workgroup: the
+// gradients are deterministic and bitwise independent of the workgroup mapping.
 //
 // Placement: both gradient kernels decode their workgroup id with the forward's
 // mappings (attn_internal.h), over (b, K/V head, key block) for dK/dV and over
@@ -80,8 +84,8 @@ __global__ __launch_bounds__(256) void attn_bwd_delta_kernel(const BwdArgs p) {
 
 // ---------------------------------------------------------------- dK, dV
 
-constexpr int kKeysPerWg = 128;
-constexpr int kQTile = 32;
+constexpr int kKeysPerWg = kBwdKeys;
+constexpr int kQTile = kBwdRows;
 // LDS operand reads issued ahead of the MFMA that consumes them, in MFMA steps.
 constexpr int kReadAhead = 1;
 
@@ -109,8 +113,14 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(const BwdArgs p) 
     const int c = lane & 31;
     const int h = lane >> 5;
 
-    // (b, K/V head g, key block n); only the block-major order bit applies
-    const Tile t = map_wid(MAPPING, ORDER, blockIdx.x, p.B, p.Hkv, p.NKV, p.NX);
+    // (b, K/V head g, key block n); only the block-major order bit applies.  With
+    // parts the blocks are (part, key block), key blocks fastest: workgroups in
+    // flight together read the same query rows.
+    Tile t = map_wid(MAPPING, ORDER, blockIdx.x, p.B, p.Hkv, p.NKV * p.parts, p.NX);
+    const int part = t.m / p.NKV;
+    t.m -= part * p.NKV;
+    const int n_parts = bwd_parts(p, CAUSAL, t.m);
+    if (part >= n_parts) return;
     const int Gs = p.Hq / p.Hkv;
     const int k0 = t.m * kKeysPerWg;
     const int kw0 = k0 + 32 * w;
@@ -135,7 +145,9 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(const BwdArgs p) 
     const int qt_begin = CAUSAL ? k0 / BQ : 0;
     const int qt_end = (p.Sq + BQ - 1) / BQ;
     const int n_qt = qt_end > qt_begin ? qt_end - qt_begin : 0;
-    const int total = Gs * n_qt;
+    // this part's steps: step0 + 0 .. total - 1
+    const int step0 = (int)((int64_t)Gs * n_qt * part / n_parts);
+    const int total = (int)((int64_t)Gs * n_qt * (part + 1) / n_parts) - step0;
 
     // Copies of tile tt into stage buffer `buf`: wave w fills 1 KiB slots 2w,
     // 2w+1 of the Q and dO tiles; wave 0 the lse rows, wave 1 the D rows (one
@@ -144,8 +156,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(const BwdArgs p) 
 #pragma unroll
     for (int i = 0; i < 2; ++i) src[i] = slot_src((2 * w + i) * 64 + lane);
     auto copy_tile = [&](const int tt, const int buf) __attribute__((always_inline)) {
-        const int hq = t.hq * Gs + tt / n_qt;
-        const int q0 = (qt_begin + tt % n_qt) * BQ;
+        const int hq = t.hq * Gs + (step0 + tt) / n_qt;
+        const int q0 = (qt_begin + (step0 + tt) % n_qt) * BQ;
         const int64_t row0 = ((int64_t)t.b * p.Hq + hq) * p.Sq + q0;
         const uint32_t left = (uint32_t)(p.Sq - q0) * ROW_BYTES;
         const uint32_t dst = lds_base + buf * STAGE;
@@ -183,7 +195,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(const BwdArgs p) 
 
     auto compute = [&](const int tt, auto buf_c) __attribute__((always_inline)) {
         constexpr int BUF = decltype(buf_c)::value;
-        const int q0 = (qt_begin + tt % n_qt) * BQ;
+        const int q0 = (qt_begin + (step0 + tt) % n_qt) * BQ;
         // Rows before the wave's first key see none of its keys (causal).
         if (CAUSAL && q0 + BQ - 1 < kw0) return;
         lds_char *const qb = lds + BUF * STAGE;
@@ -322,13 +334,23 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(const BwdArgs p) 
     }
     // no copy is left in flight here: the last tile's copies were waited for
 
+    // Without the causal mask the loop does not use the lane's key: rebuilt
+    // here instead of held in a register across the loop.
+    const int key_e = CAUSAL ? my_key : kw0 + (lane_index_here() & 31);
+    if (n_parts > 1) {
+        const int64_t slab = (int64_t)p.Skv * D;
+        float *const pk = p.part + (((int64_t)t.b * p.Hkv + t.hq) * p.parts + part) * slab;
+        float *const pv = pk + (int64_t)p.B * p.Hkv * p.parts * slab;
+        store_rows_f32(dkacc, __builtin_amdgcn_make_buffer_rsrc(pk, 0, p.Skv * D * 4, kBufferFlags),
+                       key_e, h);
+        store_rows_f32(dvacc, __builtin_amdgcn_make_buffer_rsrc(pv, 0, p.Skv * D * 4, kBufferFlags),
+                       key_e, h);
+        return;
+    }
     const __amdgpu_buffer_rsrc_t rdk = __builtin_amdgcn_make_buffer_rsrc(
         (void *)((char *)p.dk + kv_head * 2), 0, p.Skv * ROW_BYTES, kBufferFlags);
     const __amdgpu_buffer_rsrc_t rdv = __builtin_amdgcn_make_buffer_rsrc(
         (void *)((char *)p.dv + kv_head * 2), 0, p.Skv * ROW_BYTES, kBufferFlags);
-    // Without the causal mask the loop does not use the lane's key: rebuilt
-    // here instead of held in a register across the loop.
-    const int key_e = CAUSAL ? my_key : kw0 + (lane_index_here() & 31);
     store_rows(dkacc, p.scale, rdk, key_e, h);
     store_rows(dvacc, 1.0f, rdv, key_e, h);
 }
@@ -337,7 +359,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dkdv_kernel(const BwdArgs p) 
 
 template <bool CAUSAL, int MAPPING, int ORDER>
 hipError_t launch_grads(const BwdArgs &a, hipStream_t stream) {
-    const int g_kv = a.B * a.Hkv * a.NKV;
+    const int g_kv = a.B * a.Hkv * a.NKV * a.parts;
     // The dK/dV kernel's natural order already starts with the heaviest causal
     // key block; it takes only the block-major bit.
     hipLaunchKernelGGL((attn_bwd_dkdv_kernel<CAUSAL, MAPPING, (ORDER & kOrderXcdBlockMajor)>),

@@ -102,5 +102,20 @@ __device__ __forceinline__ void store_rows(const f32x16 (&acc)[DBLK], float s,
     }
 }
 
+// The same rows unscaled, as fp32.
+__device__ __forceinline__ void store_rows_f32(const f32x16 (&acc)[DBLK], __amdgpu_buffer_rsrc_t r,
+                                               int row, int h) {
+#pragma unroll
+    for (int db = 0; db < DBLK; ++db) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const f32x4 v4 = {acc[db][4 * j + 0], acc[db][4 * j + 1], acc[db][4 * j + 2],
+                              acc[db][4 * j + 3]};
+            const uint32_t off = (uint32_t)(row * D + 32 * db + 8 * j + 4 * h) * 4u;
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v4), r, (int)off, 0, 0);
+        }
+    }
+}
+
 }  // namespace bwd
 }  // namespace attn

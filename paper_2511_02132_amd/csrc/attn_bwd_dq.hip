@@ -33,6 +33,40 @@ using namespace bwd;
 constexpr int kRowsPerWg = 128;
 constexpr int kKeyTile = 64;
 
+// dK and dV of 16 keys of (b, K/V head): the sum of the key block's fp32 parts in
+// the order of the parts, for key blocks of several parts (the others are
+// written already).  Thread: 8 columns of key 16 * block + tid / 16.
+template <bool CAUSAL>
+__device__ __forceinline__ void sum_parts(const BwdArgs &p, const int block) {
+    const int blocks = (p.Skv + kBwdSumRows - 1) / kBwdSumRows;
+    const int head = block / blocks;
+    const int key = (block % blocks) * kBwdSumRows + (threadIdx.x >> 4);
+    if (key >= p.Skv) return;
+    const int n_parts = bwd_parts(p, CAUSAL, key / kBwdKeys);
+    if (n_parts == 1) return;
+    const int col = (threadIdx.x & 15) * 8;
+    const int64_t slab = (int64_t)p.Skv * D;
+    const int64_t dv_off = (int64_t)p.B * p.Hkv * p.parts * slab;
+    const float *src = p.part + (int64_t)head * p.parts * slab + (int64_t)key * D + col;
+    f32x4 acc[2][2] = {};   // dK, dV
+    for (int i = 0; i < n_parts; ++i, src += slab)
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) acc[x][e] += *(const f32x4 *)(src + x * dv_off + 4 * e);
+    const int64_t out = ((int64_t)head * p.Skv + key) * D + col;
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        const float s = x == 0 ? p.scale : 1.0f;
+        __bf16 *const dst = (__bf16 *)(x == 0 ? p.dk : p.dv) + out;
+        const f32x8 v8 = {acc[x][0][0] * s, acc[x][0][1] * s, acc[x][0][2] * s, acc[x][0][3] * s,
+                          acc[x][1][0] * s, acc[x][1][1] * s, acc[x][1][2] * s, acc[x][1][3] * s};
+        *(u32x4 *)dst = __builtin_bit_cast(u32x4, __builtin_convertvector(v8, bf16x8));
+    }
+}
+
+// Workgroups past the dQ grid add up the parts of dK and dV: memory-bound work
+// that runs beside the dQ workgroups instead of in a launch of its own.
 template <bool CAUSAL, int MAPPING, int ORDER>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(const BwdArgs p) {
     constexpr int BN = kKeyTile;
@@ -49,6 +83,11 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(const BwdArgs p) {
     const int c = lane & 31;
     const int h = lane >> 5;
 
+    const int n_dq = p.B * p.Hq * p.NBQ;
+    if ((int)blockIdx.x >= n_dq) {
+        sum_parts<CAUSAL>(p, blockIdx.x - n_dq);
+        return;
+    }
     const Tile t = map_wid(MAPPING, ORDER, blockIdx.x, p.B, p.Hq, p.NBQ, p.NX);
     const int g = t.hq / (p.Hq / p.Hkv);
     const int q_wave0 = t.m * kRowsPerWg + 32 * w;
@@ -176,7 +215,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(const BwdArgs p) {
 // The block-major order inside an XCD's piece exists for mapping 2 only.
 template <bool CAUSAL, int MAPPING>
 hipError_t launch_dq_order(const BwdArgs &a, hipStream_t stream) {
-    const int g_q = a.B * a.Hq * a.NBQ;
+    const int sums = a.parts > 1 ? a.B * a.Hkv * ((a.Skv + kBwdSumRows - 1) / kBwdSumRows) : 0;
+    const int g_q = a.B * a.Hq * a.NBQ + sums;
     switch (MAPPING == ATTN_MAP_SWIZZLED_HEAD_FIRST ? a.order : (a.order & kOrderHeavyFirst)) {
         case 0:
             hipLaunchKernelGGL((attn_bwd_dq_kernel<CAUSAL, MAPPING, 0>), dim3(g_q), dim3(256), 0, stream, a);

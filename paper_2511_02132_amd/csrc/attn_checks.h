@@ -73,6 +73,71 @@ inline int validate_lse(const float *lse, const void *q, const void *k, const vo
     return ATTN_OK;
 }
 
+inline int order_bits(int mapping) {
+    return ((mapping & ATTN_ORDER_HEAVY_FIRST) ? attn::kOrderHeavyFirst : 0) |
+           ((mapping & ATTN_ORDER_XCD_BLOCK_MAJOR) ? attn::kOrderXcdBlockMajor : 0) |
+           ((mapping & ATTN_ORDER_PAIRED) ? attn::kOrderPaired : 0);
+}
+
+// Checks of a backward call and, when they pass, its launch arguments (one part
+// per key block).
+inline int prepare_bwd(BwdArgs &a, const void *q, const void *k, const void *v, const void *o,
+                       const void *dout, const float *lse, float *delta, void *dq, void *dk,
+                       void *dv, int B, int Hq, int Hkv, int Sq, int Skv, int d, float scale,
+                       int mapping) {
+    if (!dout || !lse || !delta || !dq || !dk || !dv) return ATTN_ERR_NULL;
+    int rc = validate(q, k, v, o, B, Hq, Hkv, Sq, Skv, d, scale, mapping);
+    if (rc) return rc;
+    if (mapping & ATTN_ORDER_PAIRED) return ATTN_ERR_MAPPING;   // a forward-only order
+    if (d != 128) return ATTN_ERR_UNSUPPORTED;
+    if ((((uintptr_t)dout | (uintptr_t)dq | (uintptr_t)dk | (uintptr_t)dv) & 15u) ||
+        (((uintptr_t)lse | (uintptr_t)delta) & 3u))
+        return ATTN_ERR_ALIGN;
+    if ((((int64_t)Skv + 128) * d * 2) > INT32_MAX) return ATTN_ERR_SHAPE;
+    const int64_t qo = (int64_t)B * Hq * Sq * d * 2;
+    const int64_t kv = (int64_t)B * Hkv * Skv * d * 2;
+    const int64_t st = (int64_t)B * Hq * Sq * 4;
+    const void *in[6] = {q, k, v, o, dout, lse};
+    const int64_t in_bytes[6] = {qo, kv, kv, qo, qo, st};
+    void *out[4] = {dq, dk, dv, delta};
+    const int64_t out_bytes[4] = {qo, kv, kv, st};
+    for (int i = 0; i < 4; ++i) {
+        for (int j = 0; j < 6; ++j)
+            if (overlaps(out[i], out_bytes[i], in[j], in_bytes[j])) return ATTN_ERR_ALIAS;
+        for (int j = i + 1; j < 4; ++j)
+            if (overlaps(out[i], out_bytes[i], out[j], out_bytes[j])) return ATTN_ERR_ALIAS;
+    }
+    const int nx = attn_num_xcd();
+    if (nx < 0) return nx;
+    a = BwdArgs{};
+    a.q = q;
+    a.k = k;
+    a.v = v;
+    a.o = o;
+    a.dout = dout;
+    a.lse = lse;
+    a.delta = delta;
+    a.dq = dq;
+    a.dk = dk;
+    a.dv = dv;
+    a.B = B;
+    a.Hq = Hq;
+    a.Hkv = Hkv;
+    a.Sq = Sq;
+    a.Skv = Skv;
+    a.NBQ = (Sq + 127) / 128;
+    a.NKV = (Skv + 127) / 128;
+    if ((int64_t)B * Hkv * a.NKV > INT32_MAX || (int64_t)B * Hq * a.NBQ > INT32_MAX ||
+        ((int64_t)B * Hq * Sq + 15) / 16 > INT32_MAX)
+        return ATTN_ERR_SHAPE;
+    a.NX = nx;
+    a.order = order_bits(mapping);
+    a.scale = scale;
+    a.scale_log2 = (float)((double)scale * 1.4426950408889634073599246810019);
+    a.parts = 1;
+    return ATTN_OK;
+}
+
 // Records a HIP error for attn_last_hip_error() and returns ATTN_ERR_HIP
 // (attn_abi.cpp).
 int hip_fail(hipError_t e);

@@ -172,7 +172,37 @@ struct BwdArgs {
     int order;        // kOrder* bits
     float scale;
     float scale_log2;
+    // dK/dV over several workgroups per key block (0: one): a key block of s
+    // steps, a step being one 32-row tile of one query head of the group
+    // (bwd_steps), has ceil(s / part_steps) parts of equal length.  A key block
+    // of more than one part writes fp32 parts to `part`, which the dQ launch
+    // adds up in the order of the parts.
+    int part_steps;
+    int parts;        // workgroups per key block: those of the longest, at least 1
+    float *part;      // [2: dK, dV][B][Hkv][parts][Skv][128]
 };
+
+constexpr int kBwdKeys = 128;    // keys per workgroup of the dK/dV kernel
+constexpr int kBwdRows = 32;     // query rows per step
+
+// Steps of key block n: tiles of 32 query rows that see any of its keys, for
+// each query head of the group.
+__host__ __device__ inline int bwd_steps(bool causal, int n, int group, int Sq) {
+    const int begin = causal ? n * (kBwdKeys / kBwdRows) : 0;
+    const int end = (Sq + kBwdRows - 1) / kBwdRows;
+    return end > begin ? (end - begin) * group : 0;
+}
+
+// Parts of key block n; at least one, which writes the zeros of a key block that
+// no query sees.
+__host__ __device__ inline int bwd_parts(const BwdArgs &a, bool causal, int n) {
+    if (a.part_steps == 0) return 1;
+    const int steps = bwd_steps(causal, n, a.Hq / a.Hkv, a.Sq);
+    return steps > a.part_steps ? (steps + a.part_steps - 1) / a.part_steps : 1;
+}
+
+// Rows per workgroup of the sum of parts (256 threads, 16 per row of 128).
+constexpr int kBwdSumRows = 16;
 
 // Split forward (attn_fwd_split.hip): B * Hkv products of R = (Hq/Hkv) * Sq
 // packed query rows with the keys of a K/V head, no mask.

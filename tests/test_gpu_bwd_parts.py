@@ -1,0 +1,76 @@
+"""The backward with key blocks cut into parts (attn_bwd_ws) against the fp64 oracle
+and against one workgroup per key block (attn_bwd).  Bars as in
+test_gpu_backward.py; two correct gradients differ by at most twice the bar."""
+
+import numpy as np
+import pytest
+import torch
+
+import attn_inputs as ai
+import oracle
+import paper_2511_02132_amd as pa
+from test_gpu_backward import ALL_MAPPINGS, DEV, REL_MAX, _check, _inputs
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # B, Hq, Hkv, Sq, Skv, causal: parts that cross query heads, one-step remainders,
+    # key blocks of one part beside cut ones, key blocks no query sees, ragged ends
+    (1, 8, 1, 300, 300, True), (1, 8, 1, 300, 300, False), (1, 6, 2, 129, 513, False),
+    (1, 6, 2, 513, 129, True), (1, 4, 1, 257, 700, True), (2, 4, 2, 1000, 1000, True),
+    (1, 16, 2, 97, 33, False), (1, 2, 2, 640, 640, True),
+]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,Sq,Skv,causal", SHAPES)
+def test_parts_match_oracle_and_one_part(B, Hq, Hkv, Sq, Skv, causal):
+    n = pa.lib().attn_bwd_workspace_bytes(B, Hq, Hkv, Sq, Skv, 128, int(causal))
+    print("bwd parts", B, Hq, Hkv, Sq, Skv, causal, n // (1024 * B * Hkv * Skv), flush=True)
+    assert n > 0, "the shape is meant to be cut"
+    q, k, v, do = _inputs(B, Hq, Hkv, Sq, Skv, 8000 + Sq + Skv)
+    scale = ai.default_scale(128)
+    qd, kd, vd, dod = (t.to(DEV) for t in (q, k, v, do))
+    o, lse = pa.attn_fwd_lse(qd, kd, vd, causal=causal, scale=scale)
+    first = None
+    for m in ALL_MAPPINGS:
+        outs = [torch.full_like(t, float("nan")) for t in (qd, kd, vd)]
+        pa.attn_bwd(qd, kd, vd, o, dod, lse, *outs, causal=causal, scale=scale, mapping=m)
+        torch.cuda.synchronize()
+        if first is None:
+            first = outs
+            ref = oracle.attn_bwd_f64(*[ai.bf16_bits(t) for t in (q, k, v, do)], causal, scale)
+            for name, g, r in zip(("dq", "dk", "dv"), outs, ref):
+                _check(name, g, r)
+        assert all(torch.equal(a, b) for a, b in zip(first, outs)), m
+    # the C entry without a workspace: one workgroup per key block
+    one = [torch.full_like(t, float("nan")) for t in (qd, kd, vd)]
+    delta = torch.empty_like(lse)
+    ptrs = [t.data_ptr() for t in (qd, kd, vd, o, dod, lse, delta, *one)]
+    assert pa.lib().attn_bwd(*ptrs, B, Hq, Hkv, Sq, Skv, 128, int(causal), scale, 2) == 0
+    torch.cuda.synchronize()
+    for a, b in zip(one, first):
+        assert (a.float() - b.float()).abs().max() <= 2 * REL_MAX * a.float().abs().max() + 2e-5
+
+
+def test_parts_in_a_graph_and_without_memory(monkeypatch):
+    q, k, v, do = (t.to(DEV) for t in _inputs(1, 8, 1, 300, 300, 8100))
+    o, lse = pa.attn_fwd_lse(q, k, v, causal=True)
+    outs = [torch.empty_like(t) for t in (q, k, v)]
+    pa.attn_bwd(q, k, v, o, do, lse, *outs, causal=True)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        pa.attn_bwd(q, k, v, o, do, lse, *outs, causal=True)
+    for seed in (1, 2, 3):
+        do.copy_(ai.randn_bf16(tuple(do.shape), seed).to(DEV))
+        for t in outs:
+            t.fill_(float("nan"))
+        g.replay()
+        want = pa.attn_bwd(q, k, v, o, do, lse, causal=True)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(outs, want))
+    # no memory for the workspace: one part per key block
+    monkeypatch.setattr(pa, "_workspace", lambda *a: None)
+    for a, b in zip(pa.attn_bwd(q, k, v, o, do, lse, causal=True), want):
+        assert (a.float() - b.float()).abs().max() <= 2 * REL_MAX * b.float().abs().max() + 2e-5
+    assert np.isfinite(want[0].float().cpu().numpy()).all()

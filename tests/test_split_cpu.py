@@ -52,3 +52,43 @@ def test_workspace_plan_bounds():
         assert n <= 64 << 20
         seen.add(splits)
     assert len(seen) > 5
+
+
+def bwd(q=Q, k=K, v=V, o=O, lse=L, ws=W, n=1 << 27, B=1, Hq=8, Hkv=1, Sq=512, Skv=512, d=128,
+        causal=1, scale=0.088, mapping=2, dout=0x70000000, delta=0x80000000, dq=0x90000000,
+        dk=0xA0000000, dv=0xB0000000):
+    return pa.lib().attn_bwd_ws(q, k, v, o, dout, lse, delta, dq, dk, dv, ws, n, B, Hq, Hkv, Sq,
+                                Skv, d, causal, scale, mapping)
+
+
+@pytest.mark.parametrize("kwargs,code", [
+    (dict(dq=None), -1), (dict(B=0), -2), (dict(d=64), -3), (dict(mapping=0x42), -4),
+    (dict(scale=-1.0), -5), (dict(ws=W + 8), -6), (dict(lse=L + 2), -6), (dict(dq=Q), -8),
+    (dict(ws=Q), -8), (dict(ws=0xA0000000), -8), (dict(ws=0x80000000), -8),
+])
+def test_backward_validation_codes(kwargs, code, monkeypatch):
+    monkeypatch.setenv("ATTN_NUM_XCD", "8")   # no HIP call for the XCD count
+    assert bwd(**kwargs) == code
+
+
+def test_backward_plan_bounds():
+    """The workspace holds 2..16 whole parts and at most 512 MiB; the kernels' own count
+    of parts per key block, ceil(steps / part_steps), never exceeds it."""
+    ws = pa.lib().attn_bwd_workspace_bytes
+    assert ws(1, 8, 8, 64, 64, 64, 0) == -3 and ws(1, 3, 2, 64, 64, 128, 0) == -2
+    seen = set()
+    for B, (Hq, Hkv), Sq, Skv, causal in itertools.product(
+            (1, 2, 8), ((1, 1), (8, 1), (12, 4), (64, 8), (32, 32)), (1, 33, 300, 1111, 4096, 20000),
+            (1, 128, 129, 1111, 4096, 20000), (0, 1)):
+        n = ws(B, Hq, Hkv, Sq, Skv, 128, causal)
+        assert 0 <= n <= 512 << 20
+        if n == 0:
+            continue
+        per = 2 * B * Hkv * Skv * 128 * 4
+        parts = n // per
+        assert n == parts * per and 2 <= parts <= 16
+        longest = -(-Sq // 32) * (Hq // Hkv)
+        steps = min(-(-longest // p) for p in range(2, 17) if -(-longest // -(-longest // p)) == parts)
+        assert steps >= 4 and -(-longest // steps) == parts
+        seen.add(parts)
+    assert len(seen) > 5
