@@ -121,6 +121,12 @@ enum {
  *     | ATTN_ORDER_XCD_BLOCK_MAJOR, and for d = 128 optionally
  *     | ATTN_ORDER_PAIRED.
  *
+ * Workgroups: BLOCK_M = attn_block_m(d) rows each.  Where 256-row workgroups
+ * (d = 128) would leave compute units idle or unequally loaded, the launch
+ * decodes workgroups of 128 rows with the same mapping instead; O and lse are
+ * bitwise the same.  For d = 56 and 64 the same cases take a kernel that sums a
+ * row's weights in another way (d = 64: the fp32 sum of the fp32 exponentials).
+ *
  * Ownership: all buffers belong to the caller; nothing is retained after the
  * call returns and nothing is allocated.  The kernel is enqueued on the stream
  * set by attn_set_stream() for the calling thread (default: the null stream)
@@ -132,7 +138,8 @@ int attn_fwd(const void *q, const void *k, const void *v, void *o,
 
 /*
  * attn_fwd_probe -- attn_fwd plus a record of the placement (Sections 2.2,
- * 3.2, 3.3): the same kernel writes, for every workgroup id wid, four int32
+ * 3.2, 3.3): the kernel writes, for every workgroup id wid of BLOCK_M rows (d =
+ * 128: always the 256-row workgroups), four int32
  * values probe[4*wid + 0..3] = (b, hq, m, xcc) where (b, hq, m) is the tile
  * that WG computed and xcc the XCD it ran on (hardware register XCC_ID).
  * With ATTN_ORDER_PAIRED only the B*Hq*ceil(NB/2) workgroups of the paired
@@ -152,7 +159,8 @@ int attn_fwd_probe(const void *q, const void *k, const void *v, void *o,
  * (natural log, fp32; J_i as in attn_fwd).  For d = 128 the sum is an fp32
  * sum of the fp32 exponentials.  For d = 56 and 64 it is taken over the
  * exponentials rounded to bf16 (the weights the output product uses), so lse
- * is within ln(1 + 2^-8) < 3.9e-3 of the exact value plus fp32 rounding.
+ * is within ln(1 + 2^-8) < 3.9e-3 of the exact value plus fp32 rounding (some
+ * d = 64 launches take the fp32 sum, see attn_fwd).
  * lse : device pointer to B*Hq*Sq fp32, 4-byte aligned, owned by the caller;
  *     must not overlap q, k, v or o.  Other arguments and behaviour as
  *     attn_fwd.
@@ -301,7 +309,7 @@ int attn_fwd_persistent_noalloc(const void *q, const void *k, const void *v, voi
                                 int32_t *probe, int B, int Hq, int Hkv, int Sq, int Skv,
                                 int d, int causal, float scale, int mapping);
 
-/* Number of workgroups attn_fwd launches: B * Hq * ceil(Sq / attn_block_m(d)),
+/* Number of workgroups of BLOCK_M rows: B * Hq * ceil(Sq / attn_block_m(d)),
  * or a negative ATTN_ERR_* code for an invalid shape. */
 int64_t attn_grid_size(int B, int Hq, int Sq, int d);
 

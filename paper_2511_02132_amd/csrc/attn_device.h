@@ -72,7 +72,23 @@ __device__ __forceinline__ float xor32(float x) {
     return __shfl_xor(x, 32, 64);
 }
 
+// The calling lane's index, computed where it is called: the volatile asm is
+// neither hoisted nor merged with an earlier copy, so no register has to hold
+// the lane index across a loop.
+__device__ __forceinline__ int lane_index_here() {
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
+}
+
 __device__ __forceinline__ float exp2_hw(float x) { return __builtin_amdgcn_exp2f(x); }
+// Two floats as a bf16 pair (round to nearest even), the first in the low half.
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    const f32x2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
 __device__ __forceinline__ float log2_hw(float x) { return __builtin_amdgcn_logf(x); }
 constexpr float kLn2 = 0.69314718055994530942f;
 

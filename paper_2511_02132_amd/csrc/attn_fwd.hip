@@ -389,6 +389,8 @@ hipError_t launch_mapping(const KernelArgs &a, int mapping, int grid, hipStream_
 
 hipError_t launch_attn_fwd(const KernelArgs &a, int d, bool causal, int mapping, int grid,
                            hipStream_t stream) {
+    hipError_t e = hipSuccess;
+    if (launch_attn_fwd_mixed(a, d, causal, mapping, stream, &e)) return e;
     if (d == 128) return launch_attn_fwd_d128(a, causal, mapping, grid, stream);
     if (d == 56)
         return causal ? launch_mapping<64, 56, true>(a, mapping, grid, stream)

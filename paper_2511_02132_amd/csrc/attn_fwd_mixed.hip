@@ -1,0 +1,474 @@
+// attn_fwd_mixed.hip -- attention forward for gfx950 with 128-row workgroups
+// whose waves mix the matrix-core work of two tiles with the vector work of a
+// third; for grids that do not fill the chip with the kernels of attn_fwd.hip
+// (head dimensions 64 and 56) and attn_fwd_pp.hip (128).  The rule is
+// takes_mixed below.
+//
+// Why another kernel.  A wave of attn_fwd.hip does a tile's softmax and then its
+// MFMAs, each waiting for its LDS operand, and relies on the other three waves
+// of its SIMD to fill the gaps; attn_fwd_pp.hip needs two groups of four waves in
+// step.  With fewer workgroups than that their time is the length of a wave's
+// own chain.  Here one wave overlaps by itself, in three stages: in step n the
+// vector ALU forms the probabilities of tile n while the matrix core computes the
+// scores of tile n+1 and adds the output product of tile n-1, in slots of one
+// MFMA with its share of the vector work, the LDS operands read four slots ahead.
+// A tile of 64 keys takes a wave alone on its SIMD 0.9 us at d = 128 (1.6 in the
+// two-group kernel) and 0.6 at d = 64 (0.7).  Two such workgroups on a CU run at
+// the two-group kernel's rate less 5%: with every SIMD busy the chip is bound by
+// power (the same launch on all-zero inputs runs 1.4 times as fast), and this
+// kernel copies each K/V tile once per 128 rows instead of 256.
+//
+// At d = 128 every row goes through the same operations in the same order as in
+// attn_fwd_pp.hip, so the outputs are bitwise equal.  At d = 64 the row sum is the
+// fp32 sum of the fp32 exponentials.  At d = 56, computed as 64 with zero columns,
+// the columns of V that pad it are ones in LDS, so that O's column 56 is the row
+// sum of exactly the weights the output product uses.
+//
+// Layouts, swizzles and MFMA forms are those of attn_fwd.hip.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "attn_device.h"
+#include "attn_internal.h"
+#include "attn_numa.h"
+
+namespace attn {
+namespace {
+
+using namespace dev;
+
+// LDS operands are read this many MFMAs ahead.
+constexpr int kAhead = 4;
+
+// A step's region is cut into slots of one MFMA each, in program order.  Score
+// pairs scaled by the end of slot i (of n): 16 pairs in all, spread evenly and
+// early enough for their exponentials (one slot later) and conversions (two).
+constexpr int pairs_done(int i, int n) { return i < 0 ? 0 : i >= n - 3 ? 16 : 16 * (i + 1) / (n - 2); }
+
+// D is the head dimension the kernel computes with (128 or 64); DG <= D is that
+// of the tensors in memory (56 for DeepSeek-V3-shaped heads, Section 4.5).  Rows
+// of DG elements become D-wide rows in LDS and registers: Q's and K's missing
+// 16-byte chunk is read from an out-of-range offset, which the buffer hardware
+// turns into zeros, V's is ones, and only the first DG output columns are stored.
+template <int D, int DG, bool CAUSAL>
+__global__ __launch_bounds__(kThreads, 2) void attn_fwd_mixed_kernel(const KernelArgs p,
+                                                                     const int mapping) {
+    static_assert(DG <= D && DG % 8 == 0, "stored rows are whole 16-byte chunks of the LDS rows");
+    constexpr int BM = kBlockM;
+    constexpr int BN = kBlockN;
+    constexpr int ROW_BYTES_G = DG * 2;            // a row in memory
+    constexpr int TILE_BYTES_G = BN * ROW_BYTES_G;
+    constexpr int CHUNKS_G = DG / 8;               // 16-byte chunks stored per row
+    constexpr uint32_t kOutOfRange = 0x80000000u;  // past every descriptor: reads zero
+    constexpr int KSTEPS = D / 16;             // MFMA k-steps of S^T = K Q^T
+    constexpr bool SUM_ONES = DG < D;          // row sums from a column of ones beside V
+    static_assert(DG == D || (D == 64 && DG == 56), "the row sum is read from columns 56 and 60");
+    constexpr int DBLK = D / 32;               // 32-row blocks of O^T
+    constexpr int CHUNKS_PER_ROW = D / 8;      // 16-byte chunks per K/V row
+    constexpr int ROW_BYTES = D * 2;
+    constexpr int TILE_BYTES = BN * ROW_BYTES;
+    constexpr int IPW = TILE_BYTES / 1024 / (kThreads / 64);   // LDS-copy instructions per wave
+    static_assert(IPW * 1024 * (kThreads / 64) == TILE_BYTES, "tile not divisible");
+
+    __shared__ __attribute__((aligned(1024))) char smem[4 * TILE_BYTES];
+    lds_char *const lds = (lds_char *)smem;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave index, kept scalar
+    const int c = lane & 31;   // query column of the MFMA tiles
+    const int h = lane >> 5;   // which half of the 64 lanes
+
+    Tile t = map_wid(mapping, p.order, blockIdx.x, p.B, p.Hq, p.NB, p.NX, D != 128);
+    // uniform, which the compiler does not see through the branches on the mapping
+    t.b = __builtin_amdgcn_readfirstlane(t.b);
+    t.hq = __builtin_amdgcn_readfirstlane(t.hq);
+    t.m = __builtin_amdgcn_readfirstlane(t.m);
+    if (p.probe != nullptr && tid == 0) {
+        unsigned xcc;
+        asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
+        int32_t *rec = p.probe + 4 * (int64_t)blockIdx.x;
+        rec[0] = t.b;
+        rec[1] = t.hq;
+        rec[2] = t.m;
+        rec[3] = (int)(xcc & 0xf);
+    }
+    const int g = t.hq / (p.Hq / p.Hkv);
+
+    const int64_t q_head = ((int64_t)t.b * p.Hq + t.hq) * p.Sq * DG;
+    const int64_t kv_head = ((int64_t)t.b * p.Hkv + g) * p.Skv * DG;
+    const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)((const char *)p.q + q_head * 2), 0, p.Sq * ROW_BYTES_G, kBufferFlags);
+    const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)((char *)p.o + q_head * 2), 0, p.Sq * ROW_BYTES_G, kBufferFlags);
+    // Byte offset of 16-byte chunk `ch` of row `row` in memory (zeros past DG).
+    auto mem_chunk = [&](const int row, const int ch) -> uint32_t {
+        return ch < CHUNKS_G ? (uint32_t)(row * ROW_BYTES_G + ch * 16) : kOutOfRange;
+    };
+
+    // Q^T as the B operand: lane holds Q[row][16kk + 8h .. +7] for each k-step.
+    const int q_wave0 = t.m * BM + 32 * w;   // first query row of this wave
+    const int my_q = q_wave0 + c;
+    bf16x8 qreg[KSTEPS];
+#pragma unroll
+    for (int kk = 0; kk < KSTEPS; ++kk)
+        qreg[kk] = __builtin_bit_cast(bf16x8, load16(rq, mem_chunk(my_q, 2 * kk + h)));
+
+    // K/V tiles go straight from global memory to LDS (buffer_load ... lds):
+    // each instruction of a wave fills 1024 contiguous LDS bytes, lane j the
+    // 16 bytes at j*16, so the swizzled layout is made by choosing which
+    // global 16-byte chunk each lane fetches.  Wave w fills LDS slots
+    // (w*IPW + i)*64 + lane, i < IPW, of each tile.
+    //
+    // LDS holds two K buffers and two V buffers.  The K stream runs two tiles
+    // ahead of the V stream: step n reads K(n+1) and V(n-1).  At its top both
+    // have landed and every wave is done with K(n) and V(n-2), whose buffers then
+    // receive K(n+2) and V(n).
+    uint32_t k_src[IPW], v_src[IPW];
+#pragma unroll
+    for (int i = 0; i < IPW; ++i) {
+        const int slot = (w * IPW + i) * 64 + lane;
+        const int row = slot / CHUNKS_PER_ROW;
+        const int phys = slot % CHUNKS_PER_ROW;
+        k_src[i] = mem_chunk(row, phys ^ k_swizzle<D>(row));
+        const int seg = (phys >> 1) ^ v_swizzle<D>(row);
+        v_src[i] = mem_chunk(row, seg * 2 + (phys & 1));
+    }
+    const char *const k_head = (const char *)p.k + kv_head * 2;
+    const char *const v_head = (const char *)p.v + kv_head * 2;
+    const uint32_t kv_bytes = p.Skv * ROW_BYTES_G;
+    const uint32_t lds_base = (uint32_t)(uintptr_t)lds;
+    // Copy of tile n of K (or V) into LDS buffer `buf`; the descriptor starts
+    // at the tile, so the per-lane offsets stay fixed.  A lane of a V copy whose
+    // chunk is padding is switched off: that chunk keeps its ones.
+    auto copy_tile = [&](const char *head, const uint32_t *src, const int n, const int buf, auto is_v) __attribute__((always_inline)) {
+        const uint32_t off = (uint32_t)n * TILE_BYTES_G;
+        const i32x4 d = buffer_words(head + off, kv_bytes - off);
+#pragma unroll
+        for (int i = 0; i < IPW; ++i) {
+            const uint32_t dst =
+                __builtin_amdgcn_readfirstlane(lds_base + buf * TILE_BYTES + (w * IPW + i) * 1024);
+            if (!SUM_ONES || decltype(is_v)::value == 0 || src[i] != kOutOfRange)
+                lds_copy16(d, src[i], dst);
+        }
+    };
+    // buffers: K0, K1, V0, V1
+    auto copy_k = [&](const int n, const int kbuf) __attribute__((always_inline)) { copy_tile(k_head, k_src, n, kbuf, Int<0>{}); };
+    auto copy_v = [&](const int n, const int vbuf) __attribute__((always_inline)) { copy_tile(v_head, v_src, n, 2 + vbuf, Int<1>{}); };
+
+    const int kv_end = CAUSAL ? min((t.m + 1) * BM, p.Skv) : p.Skv;
+    const int n_tiles = (kv_end + BN - 1) / BN;
+
+    // Per-lane LDS read offsets (the buffer offsets are immediates).
+    //   K operand: row 32kb + c, logical chunk 2kk + h.
+    uint32_t k_off[KSTEPS];
+#pragma unroll
+    for (int kk = 0; kk < KSTEPS; ++kk)
+        k_off[kk] = c * ROW_BYTES + (((2 * kk + h) ^ k_swizzle<D>(c)) * 16);
+    //   V operand (transposing read, 16-lane groups): lane i = l%16 of group
+    //   gsel = (l%32)/16 addresses row 4h + i/4 of a 16-key chunk (the same
+    //   swizzle for all chunks and for the +8 rows) and columns
+    //   32db + 16gsel + 4(i%4), i.e. 32-byte segment 2db + gsel.
+    const int li = lane & 15;
+    const int gsel = (lane >> 4) & 1;
+    uint32_t v_off[DBLK];
+#pragma unroll
+    for (int db = 0; db < DBLK; ++db)
+        v_off[db] = (4 * h + (li >> 2)) * ROW_BYTES + 8 * (li & 3) +
+                    (((2 * db + gsel) ^ v_swizzle<D>(4 * h + (li >> 2))) * 32);
+
+    f32x16 oacc[DBLK];
+#pragma unroll
+    for (int db = 0; db < DBLK; ++db)
+        for (int r = 0; r < 16; ++r) oacc[db][r] = 0.0f;
+    // Online-softmax state of this lane's query row: the reference the exponents
+    // are taken against, kHeadroom above the row maximum when it was set (first
+    // tile) or raised (O and l rescaled).  Any reference gives the same result in
+    // exact arithmetic, because O and l are divided by the same factor; bf16 and
+    // fp32 keep their relative precision at 2^-kHeadroom.
+    // SUM_ONES: the row sum l is a column of O.  Otherwise the reference is the
+    // maximum itself and raised when a tile's exponentials sum to more than 2^24.
+    constexpr float kHeadroom = SUM_ONES ? 20.0f : 0.0f;
+    float mb = -__builtin_inff();   // reference, times scale * log2(e)
+    float m_ref = -__builtin_inff();
+    float l_run = 0.0f;             // !SUM_ONES: sum over this lane's keys
+    const float sl2 = p.scale_log2;
+
+    // A operands: K rows of k-step kk, key half kb2; V columns of 16-key chunk kc,
+    // block db (two transposing reads).
+    auto k_operand = [&](const int kbuf, const int kk, const int kb2) __attribute__((always_inline)) -> bf16x8 {
+        return *(const lds_bf16x8 *)(lds + kbuf * TILE_BYTES + k_off[kk] + kb2 * 32 * ROW_BYTES);
+    };
+    auto v_operand = [&](const int vbuf, const int kc, const int db) __attribute__((always_inline)) -> bf16x8 {
+        lds_char *const vb = lds + (2 + vbuf) * TILE_BYTES + v_off[db] + 16 * kc * ROW_BYTES;
+        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4 *)vb);
+        const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4 *)(vb + 8 * ROW_BYTES));
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    };
+
+    // Prologue: V's padding set to ones, K(0) and K(1) in flight; scores of tile 0.
+    if (SUM_ONES) {
+#pragma unroll
+        for (int i = 0; i < IPW; ++i)
+            if (v_src[i] == kOutOfRange) {
+                const u32x4 one4 = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+#pragma unroll
+                for (int buf = 2; buf < 4; ++buf)
+                    *(lds_u32x4 *)(lds + buf * TILE_BYTES + ((w * IPW + i) * 64 + lane) * 16) = one4;
+            }
+    }
+    copy_k(0, 0);
+    if (n_tiles > 1) copy_k(1, 1);
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    __syncthreads();
+    f32x16 s_a[2], s_b[2];   // scores of even and odd tiles
+    u32x4 p_a[4], p_b[4];    // probabilities (bf16 pairs) of even and odd tiles
+#pragma unroll
+    for (int kb2 = 0; kb2 < 2; ++kb2)
+        for (int r = 0; r < 16; ++r) s_a[kb2][r] = 0.0f;
+#pragma unroll
+    for (int kk = 0; kk < KSTEPS; ++kk)
+#pragma unroll
+        for (int kb2 = 0; kb2 < 2; ++kb2)
+            s_a[kb2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(0, kk, kb2), qreg[kk],
+                                                               s_a[kb2], 0, 0, 0);
+
+    // Step n (buffers fixed by the parity of n): probabilities of tile n on the
+    // vector ALU, between the matrix-core work that does not wait for them: the
+    // scores of tile n+1 and O^T += V^T P^T of tile n-1 (not in step 0).
+    auto tile_step = [&](const int n, auto parity, auto first, f32x16 (&s_cur)[2],
+                         f32x16 (&s_next)[2], u32x4 (&p_prev)[4], u32x4 (&p_cur)[4]) __attribute__((always_inline)) {
+        constexpr int PAR = decltype(parity)::value;   // n % 2
+        constexpr bool PV = decltype(first)::value == 0;
+        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+        __syncthreads();
+        // K(n) was read in step n-1, V(n-2) too
+        if (n + 2 < n_tiles) copy_k(n + 2, PAR);
+        copy_v(n, PAR);
+
+        const int key0 = n * BN;
+        // Mask keys past Skv and, when causal, keys after the query row.
+        const bool need_mask = (key0 + BN > p.Skv) || (CAUSAL && key0 + BN - 1 > q_wave0);
+        if (need_mask) {
+            // Register r of half kb2 holds key key0 + 32kb2 + 8(r/4) + 4h + r%4: seen
+            // iff 32kb2 + 8(r/4) + r%4 <= last.  The lane index is rebuilt here: no
+            // register holds it across the loop.
+            const int ln = lane_index_here();
+            int last = p.Skv - 1;
+            if (CAUSAL) last = min(last, q_wave0 + (ln & 31));
+            last -= key0 + 4 * (ln >> 5);
+#pragma unroll
+            for (int kb2 = 0; kb2 < 2; ++kb2)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (32 * kb2 + 8 * (r >> 2) + (r & 3) > last) s_cur[kb2][r] = -__builtin_inff();
+        }
+        // Exponentials against the current reference, rounded to bf16 (the output
+        // product's B operand) as they are formed.  Whether the reference is unset
+        // (first tile) or too low for the tile shows without a maximum over it:
+        //   SUM_ONES: in the OR of their bits, whose exponent's top bit is set iff
+        //     some p >= 2, inf or NaN, i.e. a score exceeds the row maximum the
+        //     reference was set from by 2^(kHeadroom + 1) in the exp2 domain;
+        //   else: in the tile's sum, above 2^24 or not finite.
+        // Only then is the row maximum taken, O and l rescaled and the
+        // exponentials recomputed.
+        float x[32];
+        auto scale_pair = [&](const int i) __attribute__((always_inline)) {
+#pragma unroll
+            for (int e = 2 * i; e < 2 * i + 2; ++e)
+                x[e] = __builtin_fmaf(s_cur[e >> 4][e & 15], sl2, -mb);
+        };
+        auto exp_pair = [&](const int i) __attribute__((always_inline)) {
+            x[2 * i] = exp2_hw(x[2 * i]);
+            x[2 * i + 1] = exp2_hw(x[2 * i + 1]);
+        };
+        float tsum = 0.0f;
+        auto round_pair = [&](const int i) __attribute__((always_inline)) {
+            p_cur[i >> 2][i & 3] = pack_bf16(x[2 * i], x[2 * i + 1]);
+            if (!SUM_ONES) {
+                tsum += x[2 * i];
+                tsum += x[2 * i + 1];
+            }
+        };
+        // The matrix-core work, one MFMA per slot: the scores in slots 0, 2, 4, ...,
+        // the output product in slots 1, 3, 5, ... (step 0 has none).  Operands are
+        // read kAhead slots ahead.  After the last tile the scores come from a
+        // stale (in-bounds) buffer and are not used.
+        constexpr int NM = (PV ? 2 : 1) * 2 * KSTEPS;   // slots
+        bf16x8 ring[NM];
+        auto read_operand = [&](const int i) __attribute__((always_inline)) {
+            const int j = PV ? i >> 1 : i;
+            ring[i] = (PV && (i & 1)) ? v_operand(1 - PAR, j / DBLK, j % DBLK)
+                                      : k_operand(1 - PAR, j >> 1, j & 1);
+        };
+        const f32x16 zero = {};
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) read_operand(i);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < NM; ++i) {
+            if (i + kAhead < NM) read_operand(i + kAhead);
+            const int j = PV ? i >> 1 : i;
+            if (PV && (i & 1)) {
+                const int kc = j / DBLK, db = j % DBLK;
+                oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    ring[i], __builtin_bit_cast(bf16x8, p_prev[kc]), oacc[db], 0, 0, 0);
+            } else {
+                const int kk = j >> 1, kb2 = j & 1;
+                s_next[kb2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    ring[i], qreg[kk], kk == 0 ? zero : s_next[kb2], 0, 0, 0);
+            }
+#pragma unroll
+            for (int e = pairs_done(i - 1, NM); e < pairs_done(i, NM); ++e) scale_pair(e);
+#pragma unroll
+            for (int e = pairs_done(i - 2, NM); e < pairs_done(i - 1, NM); ++e) exp_pair(e);
+#pragma unroll
+            for (int e = pairs_done(i - 3, NM); e < pairs_done(i - 2, NM); ++e) round_pair(e);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        uint32_t bits = 0;
+        if (SUM_ONES)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) bits |= p_cur[i >> 2][i & 3];
+        if (__any(SUM_ONES ? (bits & 0x40004000u) != 0 : !(tsum <= 16777216.0f))) {
+            float mx = s_cur[0][0];
+#pragma unroll
+            for (int kb2 = 0; kb2 < 2; ++kb2)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s_cur[kb2][r]);
+            // Raise the reference to the row maximum (both lane halves agree).
+            const float m_new = fmaxf(m_ref, fmaxf(mx, xor32(mx)));
+            const float alpha = exp2_hw((m_ref - m_new) * sl2);   // 0 on the first tile
+            l_run *= alpha;
+#pragma unroll
+            for (int db = 0; db < DBLK; ++db)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
+            m_ref = m_new;
+            mb = m_ref * sl2 + kHeadroom;
+            tsum = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                scale_pair(i);
+                exp_pair(i);
+                round_pair(i);
+            }
+        }
+        if (!SUM_ONES) l_run += tsum;
+    };
+
+    // Two tiles per trip so that each LDS buffer has a fixed offset.
+    tile_step(0, Int<0>{}, Int<1>{}, s_a, s_b, p_b, p_a);
+    int n = 1;
+    for (; n + 1 < n_tiles; n += 2) {
+        tile_step(n, Int<1>{}, Int<0>{}, s_b, s_a, p_a, p_b);
+        tile_step(n + 1, Int<0>{}, Int<0>{}, s_a, s_b, p_b, p_a);
+    }
+    // O^T += V^T P^T of the last tile.
+    auto last_product = [&](auto parity, u32x4 (&p_last)[4]) __attribute__((always_inline)) {
+        constexpr int PAR = decltype(parity)::value;
+        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+        __syncthreads();
+#pragma unroll
+        for (int kc = 0; kc < 4; ++kc)
+#pragma unroll
+            for (int db = 0; db < DBLK; ++db)
+                oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    v_operand(PAR, kc, db), __builtin_bit_cast(bf16x8, p_last[kc]), oacc[db], 0, 0, 0);
+    };
+    if (n < n_tiles) {
+        tile_step(n, Int<1>{}, Int<0>{}, s_b, s_a, p_a, p_b);
+        last_product(Int<1>{}, p_b);
+    } else {
+        last_product(Int<0>{}, p_a);
+    }
+
+    // O = acc / l, rounded to bf16; lane holds d = 32db + 8j + 4h + 0..3 of its row.
+    const int lane_e = lane_index_here();
+    const int my_q_e = q_wave0 + (lane_e & 31);
+    const int h_e = lane_e >> 5;
+    // Columns DG .. D-1 of V are ones: both lane halves hold one of them.
+    const float l_tot = SUM_ONES ? oacc[DBLK - 1][12] : l_run + xor32(l_run);
+    const float inv = 1.0f / l_tot;
+    store_lse(p.lse == nullptr ? nullptr : p.lse + ((int64_t)t.b * p.Hq + t.hq) * p.Sq, p.Sq, my_q_e,
+              lane_e, mb, l_tot);
+#pragma unroll
+    for (int db = 0; db < DBLK; ++db) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const f32x4 o4 = {oacc[db][4 * j + 0] * inv, oacc[db][4 * j + 1] * inv,
+                              oacc[db][4 * j + 2] * inv, oacc[db][4 * j + 3] * inv};
+            const bf16x4 ob = __builtin_convertvector(o4, bf16x4);
+            const int col = 32 * db + 8 * j + 4 * h_e;   // 4 columns, all < DG or all >= DG
+            if (col >= DG) continue;
+            const uint32_t off = (uint32_t)(my_q_e * DG + col) * 2u;
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, ob), ro, (int)off, 0, 0);
+        }
+    }
+}
+
+template <int D, int DG>
+hipError_t launch(const KernelArgs &a, bool causal, int mapping, hipStream_t stream) {
+    const int grid = a.B * a.Hq * a.NB;
+    if (causal)
+        hipLaunchKernelGGL((attn_fwd_mixed_kernel<D, DG, true>), dim3(grid), dim3(kThreads), 0,
+                           stream, a, mapping);
+    else
+        hipLaunchKernelGGL((attn_fwd_mixed_kernel<D, DG, false>), dim3(grid), dim3(kThreads), 0,
+                           stream, a, mapping);
+    return hipGetLastError();
+}
+
+// Whether this kernel takes a launch.  n1 counts its workgroups (128 rows), n2
+// those of the d = 128 two-group kernel (256 rows, one per CU).  Times in us,
+// other kernel -> this one, B = 1 unless noted:
+//  * at most one workgroup per CU: a chain of tiles each.
+//      d 128 causal H 32 S 1000  27.6 -> 19.7   no mask H 16 S 2048  45.9 -> 36.4
+//      d 64  causal H 32 S 1000  17.0 -> 14.2   no mask H 8 S 4096   51.5 -> 41.9
+//  * d 128, causal: shorter workgroups balance better, and two on a CU hide each
+//    other's start, until power binds: up to 48 blocks of 128 rows a head.
+//      H 256 S 1000 117 -> 97   H 64 S 1600 71 -> 63   H 32 S 4096 159 -> 142
+//      H 64 S 6000  543 -> 538  H 32 S 8192 466 -> 481 (not taken)
+//    With two workgroups on some CUs only (n1 to 512) it loses (H 24 S 2048 45.5
+//    -> 48) unless 256-row blocks leave half a block empty (H 24 S 1600 36.5 -> 30).
+//  * d 128, no mask: whole rounds, a full one of this kernel 1.06 of the other's, a
+//    last one with one workgroup per CU 0.75.
+//      H 48 S 2048 102 -> 94    H 24 S 3000 139 -> 123   H 64 S 4096 431 (not taken)
+//  * d 56, causal: the row sum is free of vector work here.
+//      H 128 S 2048 94.3 -> 91.5   H 32 S 8192 300 -> 275   H 128 S 8192 1071 -> 1071
+bool takes_mixed(const KernelArgs &a, int d, bool causal) {
+    constexpr int64_t kUnits = 256;
+    const int nb1 = (a.Sq + kBlockM - 1) / kBlockM;
+    const int64_t heads = (int64_t)a.B * a.Hq;
+    const int64_t n1 = heads * nb1;
+    if (n1 <= kUnits) return true;
+    if (d == 56) return causal;
+    if (d != 128) return false;
+    if (causal) return n1 > 2 * kUnits ? nb1 <= 48 : (nb1 & 1) != 0;
+    const int64_t n2 = heads * ((a.Sq + kBlockM128 - 1) / kBlockM128);
+    const int64_t rest = n1 % (2 * kUnits);
+    const double here = 1.06 * (double)(n1 / (2 * kUnits)) +
+                        (rest == 0 ? 0.0 : rest <= kUnits ? 0.75 : 1.06);
+    return here < 0.97 * (double)((n2 + kUnits - 1) / kUnits);
+}
+
+}  // namespace
+
+bool launch_attn_fwd_mixed(const KernelArgs &args, int d, bool causal, int mapping,
+                           hipStream_t stream, hipError_t *err) {
+    // The d = 128 placement record and the paired and persistent orders are in
+    // blocks of 256 rows.
+    if (d == 128 && (args.queue != nullptr || args.probe != nullptr ||
+                     (args.order & kOrderPaired) != 0))
+        return false;
+    if (!takes_mixed(args, d, causal)) return false;
+    KernelArgs a = args;
+    a.NB = (a.Sq + kBlockM - 1) / kBlockM;
+    *err = d == 128  ? launch<128, 128>(a, causal, mapping, stream)
+           : d == 64 ? launch<64, 64>(a, causal, mapping, stream)
+                     : launch<64, 56>(a, causal, mapping, stream);
+    return true;
+}
+
+}  // namespace attn

@@ -228,6 +228,10 @@ struct SplitArgs {
 // 0..3 (one kernel instantiation per combination).
 hipError_t launch_attn_fwd(const KernelArgs &args, int d, bool causal, int mapping, int grid,
                            hipStream_t stream);
+// Enqueue the 128-row mixed kernel (attn_fwd_mixed.hip) if its rule takes the
+// launch (*err is then its status); false, and nothing enqueued, otherwise.
+bool launch_attn_fwd_mixed(const KernelArgs &args, int d, bool causal, int mapping,
+                           hipStream_t stream, hipError_t *err);
 // The head-dimension-128 kernel (attn_fwd_pp.hip).
 hipError_t launch_attn_fwd_d128(const KernelArgs &args, bool causal, int mapping, int grid,
                                 hipStream_t stream);

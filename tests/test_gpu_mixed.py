@@ -1,0 +1,96 @@
+"""The 128-row mixed forward kernel (small grids) through the C entry attn_fwd.
+
+d = 128: bitwise the two-group kernel, which attn_fwd_probe always runs.  Every
+head dimension: the fp64 oracle with the bars of test_gpu_attention.py, lse within
+1e-4 for d = 128 and 64 (fp32 sums) and 4e-3 for d = 56 (sum of bf16 weights).
+"""
+
+import numpy as np
+import pytest
+import torch
+
+import attn_inputs as ai
+import oracle
+import paper_2511_02132_amd as pa
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+MAX_ABS, MEAN_ABS = 2e-2, 2e-3
+
+SHAPES = [
+    # B, Hq, Hkv, Sq, Skv, causal: 1, 2, 3 and more key tiles, ragged tiles and row
+    # blocks, one row past a block, Sq != Skv under the mask, GQA
+    (1, 2, 2, 1, 1, True), (1, 2, 1, 128, 64, False), (2, 4, 2, 129, 128, False),
+    (1, 3, 3, 127, 129, False), (1, 4, 2, 200, 192, True), (1, 2, 2, 257, 65, True),
+    (1, 2, 2, 65, 300, True), (2, 6, 2, 385, 511, False), (1, 1, 1, 700, 700, True),
+]
+
+
+def _c_fwd(q, k, v, causal, scale, mapping, lse=None):
+    B, Hq, Sq, d = q.shape
+    o = torch.full_like(q, float("nan"))
+    args = (B, Hq, k.shape[1], Sq, k.shape[2], d, int(causal), scale, mapping)
+    ptrs = [t.data_ptr() for t in (q, k, v, o)]
+    lib = pa.lib()
+    lib.attn_set_stream(torch.cuda.current_stream().cuda_stream)
+    rc = lib.attn_fwd(*ptrs, *args) if lse is None else \
+        lib.attn_fwd_lse(*ptrs, lse.data_ptr(), *args)
+    assert rc == 0
+    torch.cuda.synchronize()
+    return o
+
+
+@pytest.mark.parametrize("d", [128, 64, 56])
+@pytest.mark.parametrize("B,Hq,Hkv,Sq,Skv,causal", SHAPES)
+def test_mixed_parity(B, Hq, Hkv, Sq, Skv, causal, d):
+    print("mixed", B, Hq, Hkv, Sq, Skv, causal, d, flush=True)
+    qc, kc, vc = ai.make_qkv(B, Hq, Hkv, Sq, Skv, d, seed_base=6500 + Sq + 5 * Skv)
+    q, k, v = qc.to(DEV), kc.to(DEV), vc.to(DEV)
+    scale = ai.default_scale(d)
+    bits = [ai.bf16_bits(t) for t in (qc, kc, vc)]
+    ref = oracle.attn_fwd_f64(*bits, causal, scale)
+    ref_lse, _ = oracle.attn_row_stats_f64(*bits, None, oracle.all_rows(B, Hq, Sq), causal, scale)
+    lse = torch.full((B, Hq, Sq), float("nan"), dtype=torch.float32, device=DEV)
+    o = _c_fwd(q, k, v, causal, scale, 2, lse)
+    err = np.abs(o.float().cpu().numpy().astype(np.float64) - ref)
+    assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (err.max(), err.mean())
+    bar = 4e-3 if d == 56 else 1e-4
+    assert np.abs(lse.cpu().numpy().astype(np.float64).ravel() - ref_lse).max() <= bar
+    for m in (0, 1, 3, 0x12, 0x32):
+        assert torch.equal(_c_fwd(q, k, v, causal, scale, m), o), m
+    if d == 128:
+        two_group, _ = pa.attn_fwd_probe(q, k, v, causal=causal, scale=scale)
+        torch.cuda.synchronize()
+        assert torch.equal(two_group, o), "differs from the two-group kernel"
+
+
+def test_mixed_bitwise_on_larger_grids():
+    """d = 128 grids of several rounds that the rule takes: bitwise the two-group
+    kernel, in every order."""
+    for B, Hq, Hkv, S, causal in ((3, 64, 8, 600, True), (1, 24, 24, 3000, False),
+                                  (1, 24, 24, 1600, True)):
+        print("mixed grids", B, Hq, Hkv, S, causal, flush=True)
+        g = torch.Generator(device=DEV).manual_seed(S)
+        q, k, v = (torch.randn(B, h, S, 128, device=DEV, generator=g).bfloat16()
+                   for h in (Hq, Hkv, Hkv))
+        want, _ = pa.attn_fwd_probe(q, k, v, causal=causal)
+        for m in (2, 0, 1, 3, 0x12, 0x22, 0x32):
+            assert torch.equal(_c_fwd(q, k, v, causal, 128 ** -0.5, m), want), m
+
+
+@pytest.mark.parametrize("d", [128, 64, 56])
+def test_mixed_rising_scores(d):
+    """Scores that rise from tile to tile (the reference is raised many times) and fall
+    far below it again."""
+    B, H, S = 1, 2, 640
+    qc, kc, vc = ai.make_qkv(B, H, H, S, S, d, seed_base=6700)
+    ramp = torch.cat([torch.linspace(0.1, 40, S - 128), torch.full((128,), 0.01)])
+    kc = (qc[:, :, :1, :].float().abs() * ramp[None, None, :, None]).bfloat16()
+    qc = qc.abs()
+    scale = ai.default_scale(d)
+    for causal in (False, True):
+        ref = oracle.attn_fwd_f64(*[ai.bf16_bits(t) for t in (qc, kc, vc)], causal, scale)
+        o = _c_fwd(qc.to(DEV), kc.to(DEV), vc.to(DEV), causal, scale, 2)
+        err = np.abs(o.float().cpu().numpy().astype(np.float64) - ref)
+        assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS, (err.max(), err.mean())

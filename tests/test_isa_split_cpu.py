@@ -1,4 +1,5 @@
-"""The machine-code checks of test_isa_cpu.py for the split forward (CPU only)."""
+"""The machine-code checks of test_isa_cpu.py for the split and the mixed forward (CPU
+only)."""
 
 import re
 import subprocess
@@ -11,8 +12,8 @@ B = isa.B
 pytestmark = pytest.mark.skipif(not isa._have_hipcc(), reason="hipcc not installed")
 
 
-def test_split_kernels_machine_code(tmp_path):
-    name = "attn_fwd_split.hip"
+@pytest.mark.parametrize("name,kernels", [("attn_fwd_split.hip", 6), ("attn_fwd_mixed.hip", 6)])
+def test_machine_code(tmp_path, name, kernels):
     flags = [f for f in B.compile_flags(name) if f not in ("-fPIC", "-Wall")]
     dst = tmp_path / "split.lst"
     cmd = [B.hipcc(), *flags, "--cuda-device-only", "-S", B.CSRC + "/" + name, "-o", str(dst)]
@@ -33,11 +34,11 @@ def test_split_kernels_machine_code(tmp_path):
             assert sum(i.startswith("v_mfma_f32_32x32x16_bf16") for i in body) >= 8, kname
     assert copies > 0
     mds = isa._metadata(text)
-    assert len(mds) == 6   # two kernels for each of d = 128, 64 and 56
+    assert len(mds) == kernels   # two for each of d = 128, 64 and 56
     for md in mds:
         assert md["private_segment_fixed_size"] == "0" and md.get("vgpr_spill_count", "0") == "0"
         assert int(md.get("agpr_count", "0")) == 0
         lds = int(md["group_segment_fixed_size"])
-        # d = 128: one workgroup per CU; d = 64 and 56: two
-        per_cu = 1 if "ILi128ELi128E" in md["name"] else 2
+        # the split kernel at d = 128: one workgroup per CU; the others: two
+        per_cu = 1 if "split" in md["name"] and "ILi128ELi128E" in md["name"] else 2
         assert per_cu * lds <= 160 * 1024 and int(md["vgpr_count"]) * per_cu <= 512, md["name"]
