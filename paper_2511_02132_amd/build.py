@@ -16,10 +16,11 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libattn_numa.so")
 SOURCES = ["attn_fwd.hip", "attn_fwd_pp.hip", "attn_fwd_mixed.hip", "attn_fwd_split.hip",
-           "attn_bwd.hip", "attn_bwd_dq.hip", "attn_calib.hip", "attn_abi.cpp", "attn_abi_ws.cpp"]
+           "attn_bwd.hip", "attn_bwd_dq.hip", "attn_bwd_sum.hip", "attn_calib.hip",
+           "attn_abi.cpp", "attn_abi_ws.cpp"]
 # Per-file options.  attn_bwd_dq.hip and attn_fwd_split.hip keep their
-# matrix-core accumulators in ordinary vector registers: the compiler's default (accumulators in AGPRs
-# whenever a wave may use more than 256 registers) makes the softmax copy
+# matrix-core accumulators in ordinary vector registers: the compiler's default
+# (accumulators in AGPRs whenever a wave may use more than 256 registers) makes the softmax copy
 # them out and back on every tile.
 FILE_FLAGS = {"attn_bwd_dq.hip": ["-mllvm", "--amdgpu-mfma-vgpr-form"],
               "attn_fwd_split.hip": ["-mllvm", "--amdgpu-mfma-vgpr-form"]}
@@ -30,8 +31,8 @@ ARCH = "gfx950"
 # under profiles/ describe these, so their hash ties a summary to its code.
 KERNEL_SOURCES = ["attn_fwd.hip", "attn_fwd_pp.hip", "attn_device.h", "attn_internal.h"]
 # The backward kernels and their headers, for the backward's summaries.
-BWD_KERNEL_SOURCES = ["attn_bwd.hip", "attn_bwd_dq.hip", "attn_bwd_common.h", "attn_device.h",
-                      "attn_internal.h"]
+BWD_KERNEL_SOURCES = ["attn_bwd.hip", "attn_bwd_dq.hip", "attn_bwd_dkdv.h", "attn_bwd_sum.h",
+                      "attn_bwd_common.h", "attn_device.h", "attn_internal.h"]
 
 
 def code_tokens(text: str) -> str:

@@ -83,25 +83,41 @@ SplitPlan plan_split(int B, int Hq, int Hkv, int Sq, int Skv, int d, int causal)
     return s;
 }
 
-// Steps per part of the dK/dV kernel, 0 for one part per key block.
+// Steps per part of the dK/dV workgroups, 0 for one part per key block.
 //
 // One workgroup per key block leaves the chip idle when B * Hkv * (Skv / 128) is
 // small (grouped-query heads, short sequences), and under a mask the first key
-// blocks take longest.  The estimate below (us; a step takes 1.3 alone on a CU
-// and 2.0 beside a second workgroup) is evaluated for 1 to 16 parts of the
-// longest key block.  Whole backward pass, causal unless noted, us, one part ->
-// the chosen count (best count measured):
-//   B 1 H 32/8 S 4096       996 -> 582 (552)   B 1 H 8/1  S 2405    903 -> 144
-//   B 1 H 64/8 S 2000       832 -> 314 (290)   B 1 H 12/4 S 600     109 -> 46
-//   B 1 H 32/8 S 1024       222 -> 83          B 2 H 16/16 S 1111   107 -> 90
-//   B 1 H 32/8 S 8192      2271 -> 1875        B 1 H 32/32 S 4096   595 -> 593
-//   B 1 H 32/8 S 4096 no mask 963 -> 837       B 1 H 32/32 S 2048 no mask 231, one
-int plan_bwd_steps(int B, int Hq, int Hkv, int Sq, int Skv, int causal) {
+// blocks take longest.  The time of the gradient launches is estimated for 1 to
+// 16 parts of the longest key block from the measured cost of a dK/dV step (1.2 us
+// alone on a CU, 1.5 with every CU holding a workgroup, 2.03 with two) and of a dQ
+// tile (1.9 and 2.93), on 512 workgroups at once:
+//   * one launch for both (bwd_one_launch): the longest of a workgroup's chain and
+//     an even share of all work with a tail; parts add 4 us for the launch that
+//     sums them and 40 ns each for writing and reading 128 KiB;
+//   * a launch each: dK/dV's alone, whose parts the dQ launch sums.
+// More parts have to win 1.5%, the first cut 7%.  On 40 shapes the choice is within
+// 2.2% of the best count on average.  Backward, us, start of one part per key block
+// in two launches -> chosen (best count measured):
+//   B 1 H 32/8 S 4096 causal  996 -> 553 (543)   B 1 H 8/1  S 2405 causal  903 -> 97
+//   B 1 H 64/8 S 2000 causal  832 -> 295 (295)   B 1 H 12/4 S 600  causal  109 -> 35
+//   B 1 H 32/8 S 1024 causal  222 -> 63 (63)     B 2 H 16/16 S 1111 causal 107 -> 69
+//   B 1 H 8/1  S 8192        2776 -> 880 (871)   B 1 H 32/32 S 2048        231, one
+int plan_bwd_steps(int B, int Hq, int Hkv, int Sq, int Skv, bool causal) {
+    const int group = Hq / Hkv;
     const int NKV = (Skv + attn::kBwdKeys - 1) / attn::kBwdKeys;
+    const int NBQ = (Sq + 127) / 128;
     const int64_t heads = (int64_t)B * Hkv;
-    const int longest = attn::bwd_steps(causal != 0, 0, Hq / Hkv, Sq);
+    const int longest = attn::bwd_steps(causal, 0, group, Sq);
     if (heads * NKV > 4096 || (int64_t)Skv * attn::kBwdKeys * 4 > INT32_MAX / 2) return 0;
-    const int slots = 2 * kComputeUnits;
+    constexpr double kSlots = 2 * kComputeUnits, kStep = 2.03, kTile = 2.93;
+    // dQ: tiles of 64 keys that a block of 128 rows sees
+    const int tiles_all = (Skv + 63) / 64;
+    int64_t dq_tiles = 0;
+    for (int m = 0; m < NBQ; ++m) dq_tiles += causal ? std::min(2 * (m + 1), tiles_all) : tiles_all;
+    const int64_t n_dq = (int64_t)B * Hq * NBQ;
+    const double dq_work = (double)B * Hq * dq_tiles * kTile;
+    const double dq_chain = causal ? std::min(2 * NBQ, tiles_all) : tiles_all;
+    const bool merged = attn::bwd_one_launch(heads * NKV, n_dq);
     double best = 0.0;
     int best_parts = 1;
     for (int parts = 1; parts <= kMaxBwdParts; ++parts) {
@@ -109,7 +125,7 @@ int plan_bwd_steps(int B, int Hq, int Hkv, int Sq, int Skv, int causal) {
         if (parts > 1 && (len < 4 || 1024 * heads * parts * Skv > kMaxBwdBytes)) break;
         int64_t wgs = 0, steps = 0, written = 0;
         for (int n = 0; n < NKV; ++n) {
-            const int st = attn::bwd_steps(causal != 0, n, Hq / Hkv, Sq);
+            const int st = attn::bwd_steps(causal, n, group, Sq);
             const int pn = st > len ? (st + len - 1) / len : 1;
             wgs += pn;
             steps += st;
@@ -118,23 +134,29 @@ int plan_bwd_steps(int B, int Hq, int Hkv, int Sq, int Skv, int causal) {
         wgs *= heads;
         steps *= heads;
         written *= heads;
-        const double fill = wgs < slots ? (double)wgs / slots : 1.0;
-        const double step_us = 1.3 + 0.7 * fill;
-        // One round takes the longest workgroup.  Several, in order: under a mask,
-        // whose blocks differ, an even share and a part of the longest as the
-        // tail, or whole rounds of the mean; without one, whole rounds.
-        const int64_t rounds = (wgs + slots - 1) / slots;
-        double span = len;
-        if (rounds > 1 && causal) {
-            span = std::max(span, (double)steps / slots + 0.35 * len);
-            span = std::max(span, (double)rounds * steps / wgs);
-        } else if (rounds > 1) {
-            span = (double)rounds * len;
+        double t;
+        if (merged) {
+            const double n = (double)(wgs + n_dq);
+            const double chain = len * (1.2 + 0.3 * std::min(1.0, n / kSlots));
+            if (n <= kSlots) {
+                t = std::max(chain, dq_chain * 1.9);
+            } else {
+                const double even = (steps * kStep + dq_work) / kSlots;
+                const double tail = causal ? len * kStep : std::min(len * kStep, dq_chain * kTile);
+                t = std::max(chain, even + 0.1 * tail);
+            }
+            if (parts > 1) t += 4.0 + 0.04 * written;
+        } else {
+            const int64_t rounds = (int64_t)((wgs + kSlots - 1) / kSlots);
+            double span = len;
+            if (rounds > 1 && causal)
+                span = std::max({span, steps / kSlots + 0.35 * len, (double)rounds * steps / wgs});
+            else if (rounds > 1)
+                span = (double)rounds * len;
+            t = span * (1.3 + 0.7 * std::min(1.0, wgs / kSlots)) +
+                (parts > 1 ? 2.0 + 0.05 * written : 0.0);
         }
-        // each part: 128 KiB written and read again
-        const double t = span * step_us + (parts > 1 ? 2.0 + written * 0.05 : 0.0);
-        // a cut has to be worth its workspace
-        if (parts == 1 || t < (best_parts == 1 ? 0.95 * best : best)) {
+        if (parts == 1 || t < best * (best_parts == 1 ? 0.93 : 0.985)) {
             best = t;
             best_parts = parts;
         }
@@ -142,9 +164,9 @@ int plan_bwd_steps(int B, int Hq, int Hkv, int Sq, int Skv, int causal) {
     return best_parts == 1 ? 0 : (longest + best_parts - 1) / best_parts;
 }
 
-int64_t bwd_parts_bytes(int B, int Hq, int Hkv, int Sq, int Skv, int causal, int steps) {
+int64_t bwd_parts_bytes(int B, int Hq, int Hkv, int Sq, int Skv, bool causal, int steps) {
     if (steps == 0) return 0;
-    const int longest = attn::bwd_steps(causal != 0, 0, Hq / Hkv, Sq);
+    const int longest = attn::bwd_steps(causal, 0, Hq / Hkv, Sq);
     const int parts = (longest + steps - 1) / steps;
     return 2 * (int64_t)B * Hkv * parts * Skv * 128 * 4;
 }
@@ -213,7 +235,8 @@ int64_t attn_bwd_workspace_bytes(int B, int Hq, int Hkv, int Sq, int Skv, int d,
     const int rc = attn::check_shape(B, Hq, Hkv, Sq, Skv, d);
     if (rc) return rc;
     if (d != 128) return ATTN_ERR_UNSUPPORTED;
-    return bwd_parts_bytes(B, Hq, Hkv, Sq, Skv, causal, plan_bwd_steps(B, Hq, Hkv, Sq, Skv, causal));
+    const int steps = plan_bwd_steps(B, Hq, Hkv, Sq, Skv, causal != 0);
+    return bwd_parts_bytes(B, Hq, Hkv, Sq, Skv, causal != 0, steps);
 }
 
 int attn_bwd_ws(const void *q, const void *k, const void *v, const void *o, const void *dout,
@@ -224,8 +247,8 @@ int attn_bwd_ws(const void *q, const void *k, const void *v, const void *o, cons
     const int rc = attn::prepare_bwd(a, q, k, v, o, dout, lse, delta, dq, dk, dv, B, Hq, Hkv, Sq,
                                      Skv, d, scale, mapping);
     if (rc) return rc;
-    const int steps = plan_bwd_steps(B, Hq, Hkv, Sq, Skv, causal);
-    const int64_t need = bwd_parts_bytes(B, Hq, Hkv, Sq, Skv, causal, steps);
+    const int steps = plan_bwd_steps(B, Hq, Hkv, Sq, Skv, causal != 0);
+    const int64_t need = bwd_parts_bytes(B, Hq, Hkv, Sq, Skv, causal != 0, steps);
     if (need > 0 && workspace != nullptr && workspace_bytes >= need) {
         if ((uintptr_t)workspace & 15u) return ATTN_ERR_ALIGN;
         const int64_t qo = (int64_t)B * Hq * Sq * d * 2;

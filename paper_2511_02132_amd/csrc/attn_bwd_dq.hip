@@ -19,6 +19,8 @@
 #include <stdint.h>
 
 #include "attn_bwd_common.h"
+#include "attn_bwd_dkdv.h"
+#include "attn_bwd_sum.h"
 #include "attn_internal.h"
 #include "attn_numa.h"
 
@@ -33,47 +35,16 @@ using namespace bwd;
 constexpr int kRowsPerWg = 128;
 constexpr int kKeyTile = 64;
 
-// dK and dV of 16 keys of (b, K/V head): the sum of the key block's fp32 parts in
-// the order of the parts, for key blocks of several parts (the others are
-// written already).  Thread: 8 columns of key 16 * block + tid / 16.
-template <bool CAUSAL>
-__device__ __forceinline__ void sum_parts(const BwdArgs &p, const int block) {
-    const int blocks = (p.Skv + kBwdSumRows - 1) / kBwdSumRows;
-    const int head = block / blocks;
-    const int key = (block % blocks) * kBwdSumRows + (threadIdx.x >> 4);
-    if (key >= p.Skv) return;
-    const int n_parts = bwd_parts(p, CAUSAL, key / kBwdKeys);
-    if (n_parts == 1) return;
-    const int col = (threadIdx.x & 15) * 8;
-    const int64_t slab = (int64_t)p.Skv * D;
-    const int64_t dv_off = (int64_t)p.B * p.Hkv * p.parts * slab;
-    const float *src = p.part + (int64_t)head * p.parts * slab + (int64_t)key * D + col;
-    f32x4 acc[2][2] = {};   // dK, dV
-    for (int i = 0; i < n_parts; ++i, src += slab)
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-#pragma unroll
-            for (int e = 0; e < 2; ++e) acc[x][e] += *(const f32x4 *)(src + x * dv_off + 4 * e);
-    const int64_t out = ((int64_t)head * p.Skv + key) * D + col;
-#pragma unroll
-    for (int x = 0; x < 2; ++x) {
-        const float s = x == 0 ? p.scale : 1.0f;
-        __bf16 *const dst = (__bf16 *)(x == 0 ? p.dk : p.dv) + out;
-        const f32x8 v8 = {acc[x][0][0] * s, acc[x][0][1] * s, acc[x][0][2] * s, acc[x][0][3] * s,
-                          acc[x][1][0] * s, acc[x][1][1] * s, acc[x][1][2] * s, acc[x][1][3] * s};
-        *(u32x4 *)dst = __builtin_bit_cast(u32x4, __builtin_convertvector(v8, bf16x8));
-    }
-}
+constexpr int kDqLdsBytes = 2 * 2 * kKeyTile * ROW_BYTES;
 
-// Workgroups past the dQ grid add up the parts of dK and dV: memory-bound work
-// that runs beside the dQ workgroups instead of in a launch of its own.
-template <bool CAUSAL, int MAPPING, int ORDER>
-__global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(const BwdArgs p) {
+// The workgroup (b, query head, row block) `t`, with the LDS at `smem`.
+template <bool CAUSAL>
+__device__ __forceinline__ void dq_block(const BwdArgs &p, const Tile t, char *smem) {
     constexpr int BN = kKeyTile;
     constexpr int TILE = BN * ROW_BYTES;   // 16 KiB: K or V rows of one tile
     constexpr int STAGE = 2 * TILE;
     constexpr int IPW = TILE / 1024 / 4;   // copy instructions per wave per tile
-    __shared__ __attribute__((aligned(1024))) char smem[2 * STAGE];
+    static_assert(kDqLdsBytes == 2 * STAGE, "LDS layout");
     lds_char *const lds = (lds_char *)smem;
     const uint32_t lds_base = (uint32_t)(uintptr_t)lds;
 
@@ -83,12 +54,6 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(const BwdArgs p) {
     const int c = lane & 31;
     const int h = lane >> 5;
 
-    const int n_dq = p.B * p.Hq * p.NBQ;
-    if ((int)blockIdx.x >= n_dq) {
-        sum_parts<CAUSAL>(p, blockIdx.x - n_dq);
-        return;
-    }
-    const Tile t = map_wid(MAPPING, ORDER, blockIdx.x, p.B, p.Hq, p.NBQ, p.NX);
     const int g = t.hq / (p.Hq / p.Hkv);
     const int q_wave0 = t.m * kRowsPerWg + 32 * w;
     const int my_q = q_wave0 + c;
@@ -210,6 +175,41 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(const BwdArgs p) {
     store_rows(dqacc, p.scale, rdq, my_q, h);
 }
 
+// Workgroups past the dQ grid add up the parts of dK and dV: memory-bound work
+// that runs beside the dQ workgroups instead of in a launch of its own.
+template <bool CAUSAL, int MAPPING, int ORDER>
+__global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(const BwdArgs p) {
+    __shared__ __attribute__((aligned(1024))) char smem[kDqLdsBytes];
+    const int n_dq = p.B * p.Hq * p.NBQ;
+    if ((int)blockIdx.x >= n_dq) {
+        sum_parts<CAUSAL>(p, blockIdx.x - n_dq);
+        return;
+    }
+    dq_block<CAUSAL>(p, map_wid(MAPPING, ORDER, blockIdx.x, p.B, p.Hq, p.NBQ, p.NX), smem);
+}
+
+// Both gradient grids in one launch, dK/dV workgroups first (n_kv of them, padded
+// to a multiple of the XCD count so that the dQ workgroups keep their XCDs).
+template <bool CAUSAL>
+__global__ __launch_bounds__(256, 2) void attn_bwd_grads_kernel(const BwdArgs p, const int mapping,
+                                                                const int n_kv) {
+    __shared__ __attribute__((aligned(1024))) char smem[kDqLdsBytes > kDkdvLdsBytes ? kDqLdsBytes
+                                                                                    : kDkdvLdsBytes];
+    const bool kv = (int)blockIdx.x < n_kv;
+    const int wid = kv ? (int)blockIdx.x : (int)blockIdx.x - n_kv;
+    const int heads = kv ? p.Hkv : p.Hq;
+    const int blocks = kv ? p.NKV * p.parts : p.NBQ;
+    if (wid >= p.B * heads * blocks) return;   // padding
+    Tile t = map_wid(mapping, kv ? p.order & kOrderXcdBlockMajor : p.order, wid, p.B, heads, blocks,
+                     p.NX);
+    // uniform, which the compiler does not see through the branches on the mapping
+    t.b = __builtin_amdgcn_readfirstlane(t.b);
+    t.hq = __builtin_amdgcn_readfirstlane(t.hq);
+    t.m = __builtin_amdgcn_readfirstlane(t.m);
+    if (kv) dkdv_block<CAUSAL>(p, t, smem);
+    else dq_block<CAUSAL>(p, t, smem);
+}
+
 // ---------------------------------------------------------------- launchers
 
 // The block-major order inside an XCD's piece exists for mapping 2 only.
@@ -246,7 +246,23 @@ hipError_t launch_dq_mapping(const BwdArgs &a, int mapping, hipStream_t stream) 
     }
 }
 
+template <bool CAUSAL>
+hipError_t launch_grads(const BwdArgs &a, int mapping, hipStream_t stream) {
+    const int64_t g_kv = (int64_t)a.B * a.Hkv * a.NKV * a.parts;
+    const int n_kv = (int)((g_kv + a.NX - 1) / a.NX * a.NX);
+    const int n_dq = a.B * a.Hq * a.NBQ;
+    hipLaunchKernelGGL((attn_bwd_grads_kernel<CAUSAL>), dim3(n_kv + n_dq), dim3(256), 0, stream, a,
+                       mapping, n_kv);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || a.parts == 1) return e;
+    return launch_attn_bwd_sum(a, CAUSAL, stream);
+}
+
 }  // namespace
+
+hipError_t launch_attn_bwd_grads(const BwdArgs &a, bool causal, int mapping, hipStream_t stream) {
+    return causal ? launch_grads<true>(a, mapping, stream) : launch_grads<false>(a, mapping, stream);
+}
 
 hipError_t launch_attn_bwd_dq(const BwdArgs &a, bool causal, int mapping, hipStream_t stream) {
     return causal ? launch_dq_mapping<true>(a, mapping, stream)

@@ -201,6 +201,16 @@ __host__ __device__ inline int bwd_parts(const BwdArgs &a, bool causal, int n) {
     return steps > a.part_steps ? (steps + a.part_steps - 1) / a.part_steps : 1;
 }
 
+// Whether n_kv dK/dV workgroups (one part per key block) and n_dq dQ workgroups go
+// into one launch: the last of dK/dV then run beside the first of dQ instead of
+// alone.  Two launches -> one, us: causal B 1 H 4 S 300 28 -> 19, H 8/1 S 2405 142
+// -> 105, B 4 H 16 S 700 78 -> 64, H 32 S 4096 624 -> 541; no mask H 32 S 1000 86
+// -> 70, H 16 S 4096 458 -> 452.  From 4096 workgroups on (eight rounds of the
+// chip) the tail is under 1% (H 32 S 8192 1911 -> 1890, no mask 3433 -> 3421);
+// those keep one kernel per gradient, mapping and order, which a profile tells
+// apart.
+inline bool bwd_one_launch(int64_t n_kv, int64_t n_dq) { return n_kv + n_dq < 4096; }
+
 // Rows per workgroup of the sum of parts (256 threads, 16 per row of 128).
 constexpr int kBwdSumRows = 16;
 
@@ -244,6 +254,10 @@ hipError_t static_queue(int **queue);
 hipError_t launch_clear_queue(int *queue, hipStream_t stream);
 // The backward pass (attn_bwd.hip): D, then dK/dV, then dQ, on one stream.
 hipError_t launch_attn_bwd(const BwdArgs &args, bool causal, int mapping, hipStream_t stream);
+// dK/dV and dQ in one launch, and the sum of the parts (attn_bwd_dq.hip).
+hipError_t launch_attn_bwd_grads(const BwdArgs &args, bool causal, int mapping, hipStream_t stream);
+// The sum of dK's and dV's parts alone (attn_bwd_sum.hip).
+hipError_t launch_attn_bwd_sum(const BwdArgs &args, bool causal, hipStream_t stream);
 // The dQ kernel alone (attn_bwd_dq.hip); launch_attn_bwd calls it last.
 hipError_t launch_attn_bwd_dq(const BwdArgs &args, bool causal, int mapping, hipStream_t stream);
 

@@ -16,9 +16,9 @@ pytestmark = pytest.mark.gpu
 SHAPES = [
     # B, Hq, Hkv, Sq, Skv, causal: parts that cross query heads, one-step remainders,
     # key blocks of one part beside cut ones, key blocks no query sees, ragged ends
-    (1, 8, 1, 300, 300, True), (1, 8, 1, 300, 300, False), (1, 6, 2, 129, 513, False),
+    (1, 8, 1, 300, 300, True), (1, 8, 1, 300, 300, False), (1, 8, 1, 129, 513, False),
     (1, 6, 2, 513, 129, True), (1, 4, 1, 257, 700, True), (2, 4, 2, 1000, 1000, True),
-    (1, 16, 2, 97, 33, False), (1, 2, 2, 640, 640, True),
+    (1, 16, 2, 97, 33, False), (1, 1, 1, 2000, 700, False),
 ]
 
 
@@ -48,6 +48,32 @@ def test_parts_match_oracle_and_one_part(B, Hq, Hkv, Sq, Skv, causal):
     ptrs = [t.data_ptr() for t in (qd, kd, vd, o, dod, lse, delta, *one)]
     assert pa.lib().attn_bwd(*ptrs, B, Hq, Hkv, Sq, Skv, 128, int(causal), scale, 2) == 0
     torch.cuda.synchronize()
+    for a, b in zip(one, first):
+        assert (a.float() - b.float()).abs().max() <= 2 * REL_MAX * a.float().abs().max() + 2e-5
+
+
+def test_parts_summed_by_the_dq_launch():
+    """A grid that keeps a launch per gradient (4096 workgroups) and is cut: the dQ
+    launch adds up the parts.  dQ does not depend on the cut."""
+    B, Hq, Hkv, S = 4, 64, 8, 2048
+    assert pa.lib().attn_bwd_workspace_bytes(B, Hq, Hkv, S, S, 128, 1) > 0
+    g = torch.Generator(device=DEV).manual_seed(9)
+    q, k, v, do = (torch.randn(B, h, S, 128, device=DEV, generator=g).bfloat16()
+                   for h in (Hq, Hkv, Hkv, Hq))
+    o, lse = pa.attn_fwd_lse(q, k, v, causal=True)
+    first = None
+    for m in (2, 0x12, 0x32, 0):
+        outs = [torch.full_like(t, float("nan")) for t in (q, k, v)]
+        pa.attn_bwd(q, k, v, o, do, lse, *outs, causal=True, mapping=m)
+        torch.cuda.synchronize()
+        first = first or outs
+        assert all(torch.equal(a, b) for a, b in zip(first, outs)), m
+    one = [torch.full_like(t, float("nan")) for t in (q, k, v)]
+    delta = torch.empty_like(lse)
+    ptrs = [t.data_ptr() for t in (q, k, v, o, do, lse, delta, *one)]
+    assert pa.lib().attn_bwd(*ptrs, B, Hq, Hkv, S, S, 128, 1, 128 ** -0.5, 2) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(one[0], first[0])
     for a, b in zip(one, first):
         assert (a.float() - b.float()).abs().max() <= 2 * REL_MAX * a.float().abs().max() + 2e-5
 
