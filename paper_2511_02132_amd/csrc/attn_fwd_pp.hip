@@ -125,8 +125,11 @@ constexpr int kPPLdsBytes = kStages * 2 * kBlockN * 256 + (kQInLds ? kBlockM128 
 // dispatched kernel); otherwise each group copies its own share (the
 // persistent kernel, whose scalar registers are all in use: the extra LDS
 // addresses of the first scheme would spill).
-template <bool CAUSAL, bool B_COPIES>
-__device__ __forceinline__ void pp_tile(const KernelArgs &p, const Tile t, char *smem) {
+// before_store(): called when the last product is done, before the output is
+// normalised and stored.
+template <bool CAUSAL, bool B_COPIES, typename F>
+__device__ __forceinline__ void pp_tile(const KernelArgs &p, const Tile t, char *smem,
+                                        F before_store) {
     constexpr int D = 128;
     constexpr int BM = kBlockM128;
     constexpr int BN = kBlockN;
@@ -464,6 +467,7 @@ __device__ __forceinline__ void pp_tile(const KernelArgs &p, const Tile t, char 
         if (k + 1 < n_tiles) tile(k + 1, Int<1>{});
     }
     if (grp == 0) barrier_lds();
+    before_store();
 
     // O = acc / l, rounded to bf16; lane holds d = 32db + 8j + 4h + 0..3 of its row.
     // The wave's 32 rows are consecutive in O, so they leave through LDS as
@@ -529,17 +533,17 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_fwd_pp_kernel(const Kernel
         const int slot = t.m;
         t.m = p.NB - 1 - slot;
         record_probe(p, wid, t);
-        pp_tile<CAUSAL, true>(p, t, smem);
+        pp_tile<CAUSAL, true>(p, t, smem, [] {});
         if (slot != t.m) {
             // every wave is done with the first tile's LDS before the next copies land
             __syncthreads();
             t.m = slot;
-            pp_tile<CAUSAL, true>(p, t, smem);
+            pp_tile<CAUSAL, true>(p, t, smem, [] {});
         }
     } else {
         const Tile t = map_wid(MAPPING, ORDER, wid, p.B, p.Hq, p.NB, p.NX);
         record_probe(p, wid, t);
-        pp_tile<CAUSAL, true>(p, t, smem);
+        pp_tile<CAUSAL, true>(p, t, smem, [] {});
     }
 }
 
@@ -550,9 +554,8 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_fwd_pp_kernel(const Kernel
 // whatever order the hardware starts workgroups in.  A workgroup serves the
 // queue of the XCD it runs on (XCC_ID) and, once that queue is empty, takes
 // what is left in the others (so every tile is computed even if some XCD got
-// no workgroup).  The ticket for the next tile is requested when a tile
-// starts, so its latency hides behind the tile; the launch gap between
-// workgroups (about 5 us on MI355X) disappears.  (The paired order is for
+// no workgroup).  The ticket for the next tile is requested while a
+// tile runs, so that its latency is hidden.  (The paired order is for
 // the dispatched grid only: the queues balance the work by themselves.)
 //
 // p.queue: kQueueInts int32, zero before the launch; the last workgroup to
@@ -585,11 +588,23 @@ __global__ __launch_bounds__(kPPThreads, 1) void attn_fwd_pp_persistent_kernel(c
     __syncthreads();
     int cur = next_wid;
     while (cur >= 0) {
+        // The result of the request is needed at the end of the tile.  Under a mask
+        // it is made as late as its latency allows, before the stores: made when
+        // the tile starts, it hands out the heaviest tiles two to a workgroup, and
+        // at the end some workgroups hold a tile that others could have started
+        // (GQA B 1 H 64/8 8K: 1007 -> 928 us, MHA H 32 8K: 529 -> 472, H 8 16K:
+        // 559 -> 452; with these the form is as fast as the dispatched one).
+        // Without a mask tiles cost the same, and the early request hides all of it.
         int pending = 0;
-        if (threadIdx.x == 0) pending = atomicAdd(&queue[x], 1);   // result needed at the end
+        if (!CAUSAL && threadIdx.x == 0) pending = atomicAdd(&queue[x], 1);
         const Tile t = map_wid(MAPPING, ORDER, cur, p.B, p.Hq, p.NB, p.NX);
         record_probe(p, cur, t);
-        pp_tile<CAUSAL, false>(p, t, smem);
+        if constexpr (CAUSAL)
+            pp_tile<CAUSAL, false>(p, t, smem, [&]() __attribute__((always_inline)) {
+                if (threadIdx.x == 0) pending = atomicAdd(&queue[x], 1);
+            });
+        else
+            pp_tile<CAUSAL, false>(p, t, smem, [] {});
         if (threadIdx.x == 0) next_wid = take(pending);
         __syncthreads();
         cur = next_wid;
