@@ -61,6 +61,15 @@ __device__ __forceinline__ void lds_copy16(i32x4 rsrc, uint32_t voffset, uint32_
                  : "v"(voffset), "s"(rsrc), "s"(lds_addr)
                  : "memory", "m0");
 }
+// The same with the LDS address as a scalar base plus a constant, added on the way
+// into M0, so that a kernel with many copies keeps one scalar register for them.
+template <uint32_t OFF>
+__device__ __forceinline__ void lds_copy16_at(i32x4 rsrc, uint32_t voffset, uint32_t lds_base) {
+    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 4\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds"
+                 :
+                 : "v"(voffset), "s"(rsrc), "s"(lds_base), "n"(OFF)
+                 : "memory", "m0", "scc");
+}
 #pragma clang diagnostic pop
 
 __device__ __forceinline__ u32x4 load16(__amdgpu_buffer_rsrc_t rsrc, uint32_t byte_off) {

@@ -141,20 +141,27 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_mixed_kernel(const Kerne
     // Copy of tile n of K (or V) into LDS buffer `buf`; the descriptor starts
     // at the tile, so the per-lane offsets stay fixed.  A lane of a V copy whose
     // chunk is padding is switched off: that chunk keeps its ones.
-    auto copy_tile = [&](const char *head, const uint32_t *src, const int n, const int buf, auto is_v) __attribute__((always_inline)) {
+    const uint32_t copy_base = __builtin_amdgcn_readfirstlane(lds_base + w * IPW * 1024);
+    auto copy_tile = [&](const char *head, const uint32_t (&src)[IPW], const int n, auto buf_c) __attribute__((always_inline)) {
+        constexpr int BUF = decltype(buf_c)::value;
         const uint32_t off = (uint32_t)n * TILE_BYTES_G;
         const i32x4 d = buffer_words(head + off, kv_bytes - off);
-#pragma unroll
-        for (int i = 0; i < IPW; ++i) {
-            const uint32_t dst =
-                __builtin_amdgcn_readfirstlane(lds_base + buf * TILE_BYTES + (w * IPW + i) * 1024);
-            if (!SUM_ONES || decltype(is_v)::value == 0 || src[i] != kOutOfRange)
-                lds_copy16(d, src[i], dst);
+        auto copy = [&](auto i_c) __attribute__((always_inline)) {
+            constexpr int I = decltype(i_c)::value;
+            if (!SUM_ONES || BUF < 2 || src[I] != kOutOfRange)
+                lds_copy16_at<BUF * TILE_BYTES + I * 1024>(d, src[I], copy_base);
+        };
+        copy(Int<0>{});
+        copy(Int<1>{});
+        if constexpr (IPW == 4) {
+            copy(Int<2>{});
+            copy(Int<3>{});
         }
     };
+    static_assert(IPW == 2 || IPW == 4, "copies per wave and tile");
     // buffers: K0, K1, V0, V1
-    auto copy_k = [&](const int n, const int kbuf) __attribute__((always_inline)) { copy_tile(k_head, k_src, n, kbuf, Int<0>{}); };
-    auto copy_v = [&](const int n, const int vbuf) __attribute__((always_inline)) { copy_tile(v_head, v_src, n, 2 + vbuf, Int<1>{}); };
+    auto copy_k = [&](const int n, auto buf) __attribute__((always_inline)) { copy_tile(k_head, k_src, n, buf); };
+    auto copy_v = [&](const int n, auto buf) __attribute__((always_inline)) { copy_tile(v_head, v_src, n, Int<2 + decltype(buf)::value>{}); };
 
     const int kv_end = CAUSAL ? min((t.m + 1) * BM, p.Skv) : p.Skv;
     const int n_tiles = (kv_end + BN - 1) / BN;
@@ -217,8 +224,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_mixed_kernel(const Kerne
                     *(lds_u32x4 *)(lds + buf * TILE_BYTES + ((w * IPW + i) * 64 + lane) * 16) = one4;
             }
     }
-    copy_k(0, 0);
-    if (n_tiles > 1) copy_k(1, 1);
+    copy_k(0, Int<0>{});
+    if (n_tiles > 1) copy_k(1, Int<1>{});
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     __syncthreads();
     f32x16 s_a[2], s_b[2];   // scores of even and odd tiles
@@ -243,8 +250,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_fwd_mixed_kernel(const Kerne
         __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
         __syncthreads();
         // K(n) was read in step n-1, V(n-2) too
-        if (n + 2 < n_tiles) copy_k(n + 2, PAR);
-        copy_v(n, PAR);
+        if (n + 2 < n_tiles) copy_k(n + 2, parity);
+        copy_v(n, parity);
 
         const int key0 = n * BN;
         // Mask keys past Skv and, when causal, keys after the query row.

@@ -27,7 +27,8 @@ def test_machine_code(tmp_path, name, kernels):
             assert not isa.IMPLICIT_M0.match(op) and not isa.SCALAR_WRITE.match(op), (kname, ins)
             assert not isa.PACKED_F32.match(op), (kname, ins)
             if "m0" in ins.replace(",", " ").split():
-                assert op == "s_mov_b32" and body[j + 1] == "s_nop 4", (kname, ins)
+                assert op in ("s_mov_b32", "s_add_u32"), (kname, ins)
+                assert ins.split()[1].rstrip(",") == "m0" and body[j + 1] == "s_nop 4", (kname, ins)
                 assert re.search(r"^buffer_load_dwordx4.*\blds\b", body[j + 2]), body[j:j + 3]
                 copies += 1
         if "merge" not in kname:
