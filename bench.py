@@ -135,14 +135,17 @@ def main():
         pa.attn_fwd(q, k, v, o, causal=causal, scale=scale, mapping=mapping, stream=stream)
 
     if args.profile:
-        # Each (mapping, order) is its own kernel symbol, so one run covers all.
+        # Each (mapping, order) of the kernels for full grids is its own symbol, so one
+        # run covers all.
         for _, m in variants(causal, d):
             for _ in range(args.profile_launches):
                 step(m)
         # One workgroup (wid 0 runs on XCD 0): shows which counter instances belong to XCD 0.
         q1 = torch.zeros(1, 1, pa.block_m(128), 128, dtype=torch.bfloat16, device=dev)
         kv1 = torch.zeros(1, 1, 4096, 128, dtype=torch.bfloat16, device=dev)
-        pa.attn_fwd(q1, kv1, kv1, causal=False, mapping=pa.SWIZZLED_HEAD_FIRST, stream=stream)
+        # The probe form always runs 256-row workgroups; attn_fwd would cut the keys.
+        pa.attn_fwd_probe(q1, kv1, kv1, causal=False, mapping=pa.SWIZZLED_HEAD_FIRST,
+                          stream=stream)
         # A plain copy of known size: scales FETCH_SIZE / WRITE_SIZE to bytes.
         src = torch.ones(256 * 2 ** 20, dtype=torch.uint8, device=dev)
         dst = torch.empty_like(src)

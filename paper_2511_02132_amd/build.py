@@ -29,7 +29,8 @@ ARCH = "gfx950"
 
 # The forward kernels and the headers they include: the counter summaries
 # under profiles/ describe these, so their hash ties a summary to its code.
-KERNEL_SOURCES = ["attn_fwd.hip", "attn_fwd_pp.hip", "attn_device.h", "attn_internal.h"]
+KERNEL_SOURCES = ["attn_fwd.hip", "attn_fwd_pp.hip", "attn_fwd_mixed.hip", "attn_fwd_split.hip",
+                  "attn_device.h", "attn_internal.h"]
 # The backward kernels and their headers, for the backward's summaries.
 BWD_KERNEL_SOURCES = ["attn_bwd.hip", "attn_bwd_dq.hip", "attn_bwd_dkdv.h", "attn_bwd_sum.h",
                       "attn_bwd_common.h", "attn_device.h", "attn_internal.h"]

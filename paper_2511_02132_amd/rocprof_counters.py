@@ -49,6 +49,12 @@ def variant_of(kernel_name: str):
     return MAPPING_NAMES[int(m.group(2))] + order_suffix(int(m.group(3)))
 
 
+# Any dispatched forward kernel.  attn_fwd_mixed_kernel<d, stored d, causal> and
+# attn_fwd_split_kernel<...> take the mapping as an argument, so their names
+# carry no variant.
+FORWARD_RE = re.compile(r"attn_fwd_(?:pp_|mixed_|split_)?kernel<")
+
+
 # backward kernels: attn_bwd_dkdv_kernel<causal, mapping, order>, attn_bwd_dq_kernel<...>
 BWD_KERNEL_RE = re.compile(r"attn_bwd_(dkdv|dq)_kernel<(true|false), (\d), (\d)>")
 
@@ -67,6 +73,8 @@ def kernel_of(kernel_name: str):
             MAPPING_NAMES[int(m.group(3))] + order_suffix(int(m.group(4)))
     if "attn_bwd_delta_kernel" in kernel_name:
         return "D"
+    if "attn_bwd_grads_kernel" in kernel_name:
+        return "dK/dV and dQ"   # one launch, the mapping an argument
     return None
 
 

@@ -272,32 +272,36 @@ def l2_counters_by_launch(counters_dir: str, manifest_path: str):
     """{(B, Hq, Hkv, S, variant): {counter: value}} of the L2 counters of each launch.
 
     For the backward, one manifest entry is one attn_bwd call: its dK/dV and
-    dQ dispatches are summed (the D kernel is the same for every mapping)."""
+    dQ dispatches are summed (the D kernel is the same for every mapping).
+    Kernels whose name carries no variant (they take the mapping as an argument)
+    are matched by launch order alone."""
+    from paper_2511_02132_amd.rocprof_counters import FORWARD_RE, order_suffix
     rows = {}
     with open(os.path.join(counters_dir, "run_counter_collection.csv")) as f:
         for r in csv.DictReader(f):
             name = r["Kernel_Name"]
             v = _variant_of(name)
             kind = "fwd"
-            if v is None:
+            if "attn_bwd_grads_kernel" in name:   # dK/dV and dQ in one launch
+                kind = "grads"
+            elif v is None and not FORWARD_RE.search(name):
                 m = BWD_RE.search(name)
                 if m is None:
                     continue
                 kind = m.group(1)
-                from paper_2511_02132_amd.rocprof_counters import order_suffix
                 v = MAPPING_NAMES[int(m.group(3))] + order_suffix(int(m.group(4)))
             d = rows.setdefault(int(r["Dispatch_Id"]), {"variant": v, "kind": kind})
             d[r["Counter_Name"]] = d.get(r["Counter_Name"], 0.0) + float(r["Counter_Value"])
     launches = [rows[k] for k in sorted(rows)]
     manifest = json.load(open(manifest_path))
-    if any(rec["kind"] == "dkdv" for rec in launches):
+    if any(rec["kind"] in ("dkdv", "grads") for rec in launches):
         # backward run: drop the forward that made O and lse, and pair each dQ
         # dispatch with the dK/dV dispatch before it
         merged = []
         for rec in launches:
             if rec["kind"] == "fwd":
                 continue
-            if rec["kind"] == "dkdv":
+            if rec["kind"] in ("dkdv", "grads"):
                 merged.append(dict(rec))
             else:
                 prev = merged[-1]
@@ -311,7 +315,7 @@ def l2_counters_by_launch(counters_dir: str, manifest_path: str):
                          % (len(launches), len(manifest)))
     out = {}
     for rec, m in zip(launches, manifest):
-        if rec["variant"] != m["variant"]:
+        if rec["variant"] not in (None, m["variant"]):
             raise ValueError("launch order differs from the manifest")
         c = m["config"]
         vals = {key: rec[key] for key in L2_COUNTERS if key in rec}
