@@ -314,7 +314,7 @@ def small_workload(args, torch, dev, stream, flush, ai, pa):
     torch.cuda.synchronize()
     cold, _ = timed_variants(torch, stream, flush, st, vs, args.small_reps)
     out = {"workload": SMALL_WORKLOAD, "flop": fl, "reps": args.small_reps,
-           "note": "one launch of 8 workgroups; bound by launch latency, not by the MFMA rate",
+           "note": "one launch of 32 workgroups; bound by launch latency, not by the MFMA rate",
            "per_mapping": {}}
     for name, _ in vs:
         st_ = launch_stats(cold[name], fl)
